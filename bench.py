@@ -2,14 +2,15 @@
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload c1|c0|c2]
 
-A "step" is one full SSP-RK3 time step: three fused stage launches (DG right-hand
-side, chemistry, AT fluxes at PE interfaces, RK update, history publish; for the
-limited workload also the KXRCF/AT-WENO limiter of the stage's output).  The
+A "step" is one full SSP-RK3 time step (DG right-hand side, chemistry, AT fluxes at
+PE interfaces, RK update, history publish; for the limited workload also the
+KXRCF/AT-WENO limiter of every stage's output): three fused stage launches, or one
+launch of all stages for the one-step model without the limiter.  The
 metric counts scalar DOF updates (E (N_p+1) (3+N_s) per stage) per second, with
 the inputs resident in HBM before the timed region starts.
 
 Prints ONE JSON line.  The roofline object refers to the dominant kernel (the
-stage kernel): its average launch duration is measured with HIP events that the
+step's kernel): its average launch duration is measured with HIP events that the
 library records on the solver's stream around every launch (adg_profile).
 """
 from __future__ import annotations
@@ -83,8 +84,16 @@ def pmc_probe(args):
                       "steps": args.steps}), flush=True)
 
 
+def launches_per_step(case) -> int:
+    """Kernel launches of one time step: one for the one-step model without the limiter (all
+    stages in one kernel), else one per RK stage."""
+    if case["physics"]["model"] == "onestep" and not case["disc"].get("limiter"):
+        return 1
+    return RK_STAGES[case["disc"].get("rk", "ssprk3")]
+
+
 def euler_stage_bytes(case) -> float:
-    """Algorithmic HBM bytes of one stage launch, averaged over the three stages:
+    """Algorithmic HBM bytes of one launch per stage, averaged over the three stages:
     stage 1 reads w^n and writes w^(1) (16 B/DOF); stages 2 and 3 read w^n and
     w^(s) and write w^(s+1) (24 B/DOF); with the limiter (inside the same kernel)
     one troubled-cell flag byte per element."""
@@ -92,6 +101,14 @@ def euler_stage_bytes(case) -> float:
 
     flags = case["disc"]["n_elem"] if case["disc"].get("limiter") else 0
     return gen.dof(case) * 8.0 * (2 + 3 + 3) / 3.0 + flags
+
+
+def euler_launch_bytes(case) -> float:
+    """Algorithmic HBM bytes of one launch of the one-step model: a stage's, or, where a launch
+    is a whole step, w^n read once and w^(n+1) written once (16 B/DOF)."""
+    from workloads import gen
+
+    return gen.dof(case) * 16.0 if launches_per_step(case) == 1 else euler_stage_bytes(case)
 
 
 def detailed_stage_flops(case) -> float:
@@ -344,10 +361,9 @@ def bench_serve(n_req: int, rate, heap_gib: float, slots: int, chunk: int, preci
     return out
 
 
-def region_stage_ms(s, steps: int, graph: int = 10) -> float:
-    """Mean stage-launch duration of a solver whose step is three stage launches: HIP events
-    on its stream around `steps` steps replayed from `graph`-step HIP graphs, after one
-    untimed replay."""
+def region_launch_ms(s, steps: int, per_step: int, graph: int = 10) -> float:
+    """Mean launch duration of a solver whose step is `per_step` launches: HIP events on its
+    stream around `steps` steps replayed from `graph`-step HIP graphs, after one untimed replay."""
     import torch
 
     s.set_graph(graph)
@@ -358,7 +374,7 @@ def region_stage_ms(s, steps: int, graph: int = 10) -> float:
     s.step(steps)
     ev1.record(s.stream)
     torch.cuda.synchronize()
-    return ev0.elapsed_time(ev1) / (3 * steps)
+    return ev0.elapsed_time(ev1) / (per_step * steps)
 
 
 def hbm_points(steps: int = 20):
@@ -366,7 +382,7 @@ def hbm_points(steps: int = 20):
     the limiter, the C2 physics at E = 2^21 with it), each with its roofline against 8 TB/s: mean
     launch time from HIP events over graph-replayed steps on the solver's stream."""
     out = {}
-    for key, res, kernel, tkey in (("c0_physics_E4194304", sweep_euler([2**22], steps)[0], "euler_stage_kernel",
+    for key, res, kernel, tkey in (("c0_physics_E4194304", sweep_euler([2**22], steps)[0], "euler_step_kernel",
                                     "c0_4194304"),
                                    ("c2_physics_E2097152", sweep_limiter([2**21], steps)[0], "euler_lim_kernel",
                                     "c2_2097152")):
@@ -387,8 +403,8 @@ def served_short(n_req: int, rate: float, precision: str):
 
 
 def sweep_euler(sizes, steps=20):
-    """Size sweep of the one-step Euler stage kernel (C0 physics, N_p = 2, 8 PEs, SAA) into the
-    HBM-bound regime: per size, the stage kernel's mean launch time (HIP graphs, events over
+    """Size sweep of the one-step Euler step kernel (C0 physics, N_p = 2, 8 PEs, SAA) into the
+    HBM-bound regime: per size, its mean launch time (HIP graphs, events over
     the timed steps) and its algorithmic bandwidth."""
     import torch
 
@@ -408,8 +424,8 @@ def sweep_euler(sizes, steps=20):
         s = adg.Solver(case)
         s.set_state(w0)
         s.step(3)
-        ms = region_stage_ms(s, steps)
-        nbytes = euler_stage_bytes(case)
+        ms = region_launch_ms(s, steps, launches_per_step(case))
+        nbytes = euler_launch_bytes(case)
         out.append({"n_elem": E, "dof": gen.dof(case), "stage_ms": ms, "GBps": nbytes / (ms * 1e-3) / 1e9,
                     "frac_hbm": nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "bytes": nbytes})
         s.close()
@@ -446,7 +462,7 @@ def sweep_ns(sizes, steps=20):
         s.set_state(w0)
         cfg = s.autotune()
         s.set_state(w0)
-        ms = region_stage_ms(s, steps)
+        ms = region_launch_ms(s, steps, launches_per_step(case))
         flops = detailed_stage_flops(case)
         try:
             s.sync()              # raises if the run latched a state error
@@ -479,8 +495,8 @@ def sweep_limiter(sizes, steps=20):
         s = adg.Solver(case)
         s.set_state(w0)
         s.step(3)
-        ms = region_stage_ms(s, steps)
-        nbytes = euler_stage_bytes(case)
+        ms = region_launch_ms(s, steps, launches_per_step(case))
+        nbytes = euler_launch_bytes(case)
         out.append({"n_elem": E, "dof": gen.dof(case), "stage_ms": ms, "GBps": nbytes / (ms * 1e-3) / 1e9,
                     "frac_hbm": nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "bytes": nbytes})
         s.close()
@@ -565,7 +581,7 @@ def main():
               flush=True)
         return
     if args.sweep_euler:
-        print(json.dumps({"sweep": "euler_stage_kernel", "results": sweep_euler([2**p for p in range(10, 24, 1)])}),
+        print(json.dumps({"sweep": "euler_step_kernel", "results": sweep_euler([2**p for p in range(10, 24, 1)])}),
               flush=True)
         print(json.dumps({"sweep": "euler_lim_kernel", "results": sweep_limiter([2**p for p in range(13, 23, 1)])}),
               flush=True)
@@ -596,10 +612,9 @@ def main():
     value = dof * 3 * args.steps / el
     ms_per_step = el * 1e3 / args.steps
 
-    # dominant kernel: the stage kernel, the only kernel of a step (one launch per RK stage):
-    # its mean launch duration is the HIP-event time of the timed region on the solver's
-    # stream over the launches in it
-    stage_ms = ev0.elapsed_time(ev1) / (args.steps * RK_STAGES[case["disc"].get("rk", "ssprk3")])
+    # dominant kernel: the only kernel of a step; its mean launch duration is the HIP-event time
+    # of the timed region on the solver's stream over the launches in it
+    stage_ms = ev0.elapsed_time(ev1) / (args.steps * launches_per_step(case))
     # each launch alone between its own pair of events (includes its dispatch), for reference
     prof = s.profile(max(10, min(args.steps, 50)))
     detailed = case["physics"]["model"] == "detailed"
@@ -612,11 +627,11 @@ def main():
                 "frac": achieved / FP64_VECTOR_PEAK_TFLOPS, "traffic": read_traffic(traffic_key, kernel_src),
                 "kernel": "ns_stage_kernel", "launch_ms": stage_ms, "flops_per_launch": flops}
     else:
-        nbytes = euler_stage_bytes(case)
+        nbytes = euler_launch_bytes(case)
         achieved = nbytes / (stage_ms * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": read_traffic(traffic_key, kernel_src),
-                "kernel": "euler_lim_kernel" if case["disc"].get("limiter") else "euler_stage_kernel",
+                "kernel": "euler_lim_kernel" if case["disc"].get("limiter") else "euler_step_kernel",
                 "launch_ms": stage_ms, "bytes_per_launch": nbytes}
     d = case["disc"]
     out = {

@@ -202,8 +202,9 @@ int32_t adg_n_interfaces(const adg_solver *s);
 /* Enqueue n_steps steps like adg_step and time every kernel launch with HIP
    events on the solver's stream.  ms_out[i] receives the mean duration in ms
    of kernel class i and launches_out[i] the launch count; n_classes is the
-   array length (class 0: the stage kernel, which includes the limiter of a
-   limited problem; there is one launch per RK stage).
+   array length (class 0: the step's kernel, which includes the limiter of a
+   limited problem; there is one launch per RK stage, or one per step for the
+   one-step model without the limiter).
    Synchronises. */
 adg_status adg_profile(adg_solver *s, int32_t n_steps, double *ms_out, int64_t *launches_out, int32_t n_classes);
 

@@ -100,14 +100,28 @@ void set_at_buffers(const adg_solver *s, NsArgs &a, int stage) {
 // The state buffer and step counter parity after one time step from (cur, par).
 void next_alignment(const adg_solver *s, int &cur, int &par) {
   const int S = s->P.lay.S;
-  if (rk_stage(s->P.disc.rk, 0).two_n) cur = (cur + S) % 2;
-  else if (s->P.disc.limiter && s->P.phys.model == ADG_ONESTEP) cur = 1 - cur;
+  if (s->P.phys.model == ADG_ONESTEP && !s->P.disc.limiter) cur = 1 - cur;
+  else if (rk_stage(s->P.disc.rk, 0).two_n) cur = (cur + S) % 2;
+  else if (s->P.phys.model == ADG_ONESTEP) cur = 1 - cur;
   par ^= 1;   // the step's last launch wrote the next count into the other counter
 }
 
 adg_status enqueue_step(adg_solver *s, hipStream_t st, TimerFn timer) {
   const int M = s->P.lay.M, S = s->P.lay.S;
   const int rk = s->P.disc.rk;
+  if (s->P.phys.model == ADG_ONESTEP && !s->P.disc.limiter) {
+    // the whole step in one launch; its halo lanes read other wavefronts' elements, so the
+    // state alternates between buffers 0 and 1
+    EulerArgs a = s->P.ea;
+    a.ws = s->P.W[s->cur];
+    a.wout = s->P.W[1 - s->cur];
+    a.par = s->par;
+    if (timer) timer(s, 0, true);
+    HIP_TRY(s, launch_euler_step(M, s->P.disc.flux, S, a, st));
+    if (timer) timer(s, 0, false);
+    next_alignment(s, s->cur, s->par);
+    return ADG_OK;
+  }
   const int in_buf[3] = {0, 1, 2}, out_buf[3] = {1, 2, 0};
   for (int stage = 0; stage < S; ++stage) {
     const RkStage r = rk_stage(rk, stage);
@@ -117,19 +131,19 @@ adg_status enqueue_step(adg_solver *s, hipStream_t st, TimerFn timer) {
     // stage 3 to the other one again.  2N schemes: the state alternates between buffers
     // 0 and 1 (s->cur holds it at the start of the step), the register is buffer 2
     // (with the limiter, buffers 2 and 3 alternate the same way).
-    const bool alt = !r.two_n && s->P.disc.limiter && s->P.phys.model == ADG_ONESTEP;
+    const bool limited = s->P.phys.model == ADG_ONESTEP;
+    const bool alt = !r.two_n && limited;
     const int lim_in[3] = {s->cur, 1 - s->cur, 2}, lim_out[3] = {1 - s->cur, 2, 1 - s->cur};
     const int bi = r.two_n ? (s->cur + stage) % 2 : alt ? lim_in[stage] : in_buf[stage];
     const int bo = r.two_n ? (s->cur + stage + 1) % 2 : alt ? lim_out[stage] : out_buf[stage];
     const bool last = stage == S - 1;
-    if (s->P.phys.model == ADG_ONESTEP) {
-      const bool lim = s->P.disc.limiter != 0;
+    if (limited) {
       EulerArgs a = s->P.ea;
       a.alt = 0;   // buffers chosen here (the batched kernels choose them by step parity)
       a.w0 = s->P.W[alt ? s->cur : 0];
       a.ws = s->P.W[bi];
       a.wout = s->P.W[bo];
-      if (lim && r.two_n) {
+      if (r.two_n) {
         // the two registers alternate like the state: read W[2 + bi], write W[2 + bo]
         a.kbuf = s->P.W[2 + bi];
         a.kout = s->P.W[2 + bo];
@@ -139,7 +153,7 @@ adg_status enqueue_step(adg_solver *s, hipStream_t st, TimerFn timer) {
       a.advance = last;
       a.par = s->par;
       if (timer) timer(s, 0, true);
-      HIP_TRY(s, launch_euler_stage(M, s->P.disc.flux, a, lim ? &s->P.la : nullptr, st));
+      HIP_TRY(s, launch_euler_lim(M, s->P.disc.flux, a, s->P.la, st));
       if (timer) timer(s, 0, false);
     } else {
       NsArgs a = s->P.na;
@@ -385,9 +399,8 @@ adg_status adg_profile(adg_solver *s, int32_t n_steps, double *ms_out, int64_t *
     adg_status rc = enqueue_step(s, s->stream, prof_timer);
     if (rc != ADG_OK) return rc;
   }
-  // the launch classes of one step, in order
-  std::vector<int> order;
-  for (int stage = 0; stage < s->P.lay.S; ++stage) order.push_back(0);
+  // the launches of one step, all of class 0
+  const std::vector<int> order(s->prof_events.size() / 2 / n_steps, 0);
   HIP_TRY(s, hipStreamSynchronize(s->stream));
   std::vector<double> sum(n_classes, 0.0);
   std::vector<int64_t> cnt(n_classes, 0);

@@ -8,8 +8,9 @@
 //
 // A time step launches, per stage, one batched kernel for all detailed-
 // chemistry instances (orders dispatched inside the kernel) and one batched
-// kernel per (order, flux, limiter) group of one-step instances, the limiter of
-// limited instances inside that kernel.  Every workgroup works on one instance
+// kernel per (order, flux) group of limited one-step instances, the limiter
+// inside that kernel; unlimited one-step instances take one launch per (order,
+// flux) group and step.  Every workgroup works on one instance
 // only, with that instance's own arguments, so the arithmetic of an instance
 // does not depend on what else is in the batch.
 #include <hip/hip_runtime.h>
@@ -197,7 +198,7 @@ void rebuild_tiles(adg_batch *b) {
                     return s.P.phys.model == ADG_ONESTEP && s.P.lay.M == M && s.P.disc.flux == flux &&
                            (s.P.disc.limiter != 0) == (lim != 0);
                   },
-                  [&](const Slot &s) { return euler_blocks(s.P.lay.E, lim != 0); });
+                  [&](const Slot &s) { return euler_blocks(s.P.lay.E, lim ? kEulerLimOwned : kEulerStepOwned); });
 }
 
 // The extra streams and events of concurrent group launches, created on first use.
@@ -226,6 +227,7 @@ adg_status enqueue_batch_step(adg_batch *b, hipStream_t st, bool timed) {
     }
     for (int gi = 0; gi < (int)b->groups.size(); ++gi) {
       const Group &g = b->groups[gi];
+      if (g.kind == 1 && !g.lim && stage > 0) continue;   // its whole step ran in the first launch
       const hipStream_t gs = nstreams > 1 && gi % nstreams ? b->aux[gi % nstreams - 1] : st;
       hipEvent_t e0 = nullptr, e1 = nullptr;
       if (timed) {
@@ -440,7 +442,7 @@ adg_status adg_batch_add(adg_batch *b, const adg_physics *phys, const adg_discre
     std::memset(&es, 0, sizeof es);
     const int in_buf[3] = {0, 1, 2}, out_buf[3] = {1, 2, 0};
     for (int st = 0; st < 3; ++st) {
-      EulerArgs a = P.ea;   // with the limiter a.alt is set: the kernel picks the buffers
+      EulerArgs a = P.ea;   // a.alt is set: the kernel picks the buffers
       a.w0 = P.W[0];
       a.ws = P.W[in_buf[st]];
       a.wout = P.W[out_buf[st]];
@@ -532,7 +534,7 @@ adg_status adg_batch_get_state(adg_batch *b, int32_t slot, double *w, int64_t co
   const Layout &L = P.lay;
   const int VM = L.V * L.M;
   if (count != (int64_t)L.E * VM) return bfail(b, ADG_ERR_ARG, "state size mismatch");
-  // with the limiter the state lives in buffer (step count) mod 2
+  // one-step instances: the state lives in buffer (step count) mod 2
   const double *src = P.W[0];
   if (P.ea.alt) {
     long long n = 0;

@@ -1,13 +1,13 @@
-// Stage kernel of the one-step reactive Euler model, with the troubled-cell
-// indicator and the characteristic (AT-)WENO limiter of a limited problem in the
-// same kernel.
+// Kernels of the one-step reactive Euler model: a whole time step per launch without the
+// limiter (euler_step_body), one stage per launch with the troubled-cell indicator and the
+// characteristic (AT-)WENO limiter in the same kernel (euler_stage_body).
 //
 // Stage (Sec. 3.1 Eq. (5), Sec. 3.2 Eq. (7)): one thread per element; each
-// wavefront owns 62 consecutive elements (60 with the limiter) and holds one
-// neighbour (two with the limiter) on each side.  Every lane loads its element's
+// wavefront owns consecutive elements and holds neighbours on each side (one lane per
+// stage of the launch, two with the limiter).  Every lane loads its element's
 // modal DoFs from the component planes (coalesced) and forms both face traces;
 // one numerical flux per face is computed and passed to the neighbouring lane by
-// a shuffle; at PE-interface faces the synchronous flux of this level is written
+// a lane shift; at PE-interface faces the synchronous flux of this level is written
 // to the history ring and replaced by the AT combination of past levels.  The
 // volume integral, the source projection, the lift and the RK combination then
 // run in registers and the output is stored once.
@@ -19,7 +19,7 @@
 // in place of the unlimited ones with no further pass (every stencil still sees
 // unlimited data, the simultaneous application of the limiter).  HBM traffic per
 // stage: read w^(s) (+ w^n for stages 2 and 3), write w^(s+1), plus a flag byte
-// per element with the limiter.
+// per element.
 #include "adg_device.hpp"
 
 namespace adg {
@@ -50,7 +50,7 @@ __device__ __forceinline__ void load_elem(const double *__restrict__ w, int E, i
 // The AT flux of Eq. (7) at PE interface i with delay k > 0: the past levels' synchronous
 // fluxes of this stage combined with the Eq. (8) weights.  Levels 0..3 are loaded together
 // (a level past q reads level n-k with weight 0), later ones (q > 4) one at a time.
-__device__ __forceinline__ void at_flux(const EulerArgs &a, int nmod, int i, int k, double (&acc)[5]) {
+__device__ __forceinline__ void at_flux(const EulerArgs &a, int nmod, int stage, int i, int k, double (&acc)[5]) {
 #pragma unroll
   for (int v = 0; v < 5; ++v) acc[v] = 0.0;
   const int q = a.dl.q;
@@ -58,13 +58,13 @@ __device__ __forceinline__ void at_flux(const EulerArgs &a, int nmod, int i, int
   for (int j = 0; j < 4; ++j) {
     const bool in = j < q;
     const double c = in ? at_weight(q, k, j) : 0.0;
-    const double *h = ring_at(a.ring, ring_slot(nmod, k + (in ? j : 0), a.ring.D), a.stage, a.dl.nif, i) + a.ring.off_F;
+    const double *h = ring_at(a.ring, ring_slot(nmod, k + (in ? j : 0), a.ring.D), stage, a.dl.nif, i) + a.ring.off_F;
 #pragma unroll
     for (int v = 0; v < 5; ++v) acc[v] += c * h[v];
   }
   for (int j = 4; j < q; ++j) {
     const double c = at_weight(q, k, j);
-    const double *h = ring_at(a.ring, ring_slot(nmod, k + j, a.ring.D), a.stage, a.dl.nif, i) + a.ring.off_F;
+    const double *h = ring_at(a.ring, ring_slot(nmod, k + j, a.ring.D), stage, a.dl.nif, i) + a.ring.off_F;
 #pragma unroll
     for (int v = 0; v < 5; ++v) acc[v] += c * h[v];
   }
@@ -438,7 +438,183 @@ __device__ __forceinline__ void gather_first_slots(const EulerArgs &a, int nmod,
   }
 }
 
-// ---------------------------------------------------------------- stage kernel
+// ---------------------------------------------------------------- step kernel (no limiter)
+
+// LDS doubles per wavefront: the AT fluxes of the lanes' faces for every stage of the step.
+template <int S>
+constexpr int fat_wave_doubles() { return S * 5 * 64; }
+
+// One whole time step (S stages) of a problem without the limiter.  Lane l of a wavefront holds
+// element base + l - S (base = (64 - 2S) * wavefront index): the lanes S .. 63-S own their element,
+// the S lanes on each side hold neighbours.  Stage s forms the lanes s+1 .. 62-s, which is what the
+// stages after it need, so the state is read once and written once per step (16 B per scalar DOF,
+// where one launch per stage moves 64 B for SSP-RK3) and a small problem pays one launch and one
+// memory latency per step instead of S.  Against one launch per stage (N_p = 2, SSP-RK3): 11.3 us per
+// step against 21.7 at E = 512 (launch and latency bound), 0.33 ms against 0.78 at E = 2^22 (was bound
+// by HBM at 5.2 TB/s; now by the FP64 issue rate, 3.0 TB/s of the one read and one write).  The halo
+// lanes repeat their owners' arithmetic bit for bit (6 of 64 lanes for SSP-RK3, 10 for the five-stage
+// scheme).  Past levels' fluxes are all that a
+// delayed face reads from the ring, and those precede the step, so every stage's AT flux is formed
+// at the start, beside the state loads, and kept in LDS by its own lane (no barrier).
+template <int M, int FLUX, int S>
+__device__ __forceinline__ void euler_step_body(const EulerArgs &a, const double *win, double *wout, double *lds,
+                                                int blk, long long n, int par) {
+  constexpr int V = 5, Q = M, H = S, WE = 64 - 2 * H;
+  constexpr int RK = S == 3 ? 0 : S == 2 ? 1 : 2;
+  const int lane = threadIdx.x & 63;
+  const int base = ((blk * kEulerBlock + threadIdx.x) >> 6) * WE;
+  const int E = a.E;
+  if (base < E) {
+    const int xu = base + lane - H;                       // element index before periodic wrap
+    const bool periodic = a.periodic != 0;
+    // an element of the mesh, or its periodic image within the halo
+    const bool inside = periodic ? xu <= E - 1 + H : (xu >= 0 && xu < E);
+    const bool own = lane >= H && lane < 64 - H && xu < E;
+    const bool ghost_l = !periodic && xu == -1;           // transmissive ends: ghost = interior trace
+    const bool ghost_r = !periodic && xu == E;
+    // face xu + 1, right of the lane's element
+    const bool face_lane = lane <= 62 && (periodic ? xu + 1 <= E - 1 + H : (xu >= -1 && xu < E));
+    int x = xu, fidx = xu + 1;
+    if (periodic) {   // within a few periods of [0, E)
+      while (x < 0) x += E;
+      while (x >= E) x -= E;
+      fidx = x + 1;   // face E is face 0
+    }
+    const int iface = face_lane ? a.face_if[fidx] : -1;
+    const int nmod = step_mod(n, a.ring.D);
+    double u[V][M], wn[V][M];
+    if (inside) {
+      load_elem<M>(win, E, x, u);
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int j = 0; j < M; ++j) u[v][j] = 0.0;
+    }
+    const int kf = iface >= 0 ? eff_delay(a.dl, n, iface) : 0;
+    double *fat = lds + (threadIdx.x >> 6) * fat_wave_doubles<S>() + lane;
+    if (kf > 0) {
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        double F[V];
+        at_flux(a, nmod, s, iface, kf, F);
+#pragma unroll
+        for (int v = 0; v < V; ++v) fat[(s * V + v) * 64] = F[v];
+      }
+    }
+    // the second operand of the RK combination: w^n, or the 2N register
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+      for (int j = 0; j < M; ++j) wn[v][j] = RK == 0 ? u[v][j] : 0.0;
+    bool ok = true;
+#pragma unroll 1
+    for (int s = 0; s < S; ++s) {
+      const RkStage rk = rk_stage(RK, s);
+      const double ca = rk.ca, cb = rk.cb;
+      const bool use_prev = s > 0;
+      // the lanes whose output a later stage or the store needs
+      const bool calc = lane > s && lane < 63 - s && (periodic ? xu <= E + H - 2 - s : inside);
+      double wl[V], wr[V], F[V], Fl[V];
+      traces<M>(u, wl, wr);
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const double next_l = dpp_move<kDppFromNext>(wl[v]);
+        const double prev_r = dpp_move<kDppFromPrev>(wr[v]);
+        if (ghost_l) wr[v] = next_l;
+        if (ghost_r) wl[v] = prev_r;
+      }
+      double wp[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) wp[v] = dpp_move<kDppFromNext>(wl[v]);
+      const bool fok = numflux1<FLUX>(a.ph, wr, wp, F);
+      // faces that an owned element has
+      if (face_lane && lane >= H - 1 && lane < 64 - H && xu < E) ok = fok && ok;
+      if (iface >= 0) {
+        if (own) {   // the face's owner publishes the synchronous flux of this level
+          double *rec = ring_at(a.ring, nmod, s, a.dl.nif, iface) + a.ring.off_F;
+#pragma unroll
+          for (int v = 0; v < V; ++v) rec[v] = F[v];
+        }
+        if (kf > 0) {
+#pragma unroll
+          for (int v = 0; v < V; ++v) F[v] = fat[(s * V + v) * 64];
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < V; ++v) Fl[v] = dpp_move<kDppFromPrev>(F[v]);
+      if (calc) {
+        // b_j = sum_q w_q P_j'(xi_q) f_q - F_{e+1} P_j(1) + F_e P_j(-1); the face terms go in first
+        double vol[V][M], srcR[M];
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+          srcR[j] = 0.0;
+#pragma unroll
+          for (int v = 0; v < V; ++v) vol[v][j] = -F[v] + ((j & 1) ? -Fl[v] : Fl[v]);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          double wq[V];
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            double acc = 0.0;
+#pragma unroll
+            for (int j = 0; j < M; ++j) acc += u[v][j] * a.tb.B[q][j];
+            wq[v] = acc;
+          }
+          Prim1 pr;
+          ok = prim1(a.ph, wq, pr) && ok;
+          double f[V];
+          flux1(wq, pr, f);
+          const double rate = a.ph.k_pre * wq[3] * exp(-a.ph.e_act * (pr.rho / pr.p));
+#pragma unroll
+          for (int j = 0; j < M; ++j) {
+            const double g = a.tb.WG[q][j];
+#pragma unroll
+            for (int v = 0; v < V; ++v) vol[v][j] += g * f[v];
+            srcR[j] += a.tb.WB[q][j] * (-rate);
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+#pragma unroll
+          for (int j = 0; j < M; ++j) {
+            const double half2j1 = 0.5 * (2 * j + 1);
+            double sr = 0.0;
+            if (v == 3) sr = srcR[j];
+            if (v == 4) sr = -srcR[j];
+            const double L = a.two_over_dx * (half2j1 * vol[v][j]) + half2j1 * sr;
+            // explicit fused multiply-adds: every kernel that runs this combination rounds alike
+            if constexpr (RK == 0) {
+              const double y = fma(a.dt, L, u[v][j]);
+              u[v][j] = use_prev ? fma(ca, wn[v][j], cb * y) : y;
+            } else {
+              const double kn = use_prev ? fma(ca, wn[v][j], a.dt * L) : a.dt * L;
+              wn[v][j] = kn;
+              u[v][j] = fma(cb, kn, u[v][j]);
+            }
+          }
+        }
+      }
+    }
+    if (own) {
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int j = 0; j < M; ++j) wout[sidx(x, v * M + j, V * M)] = u[v][j];
+    }
+    if (!ok) atomicOr(a.err, (int)kErrState);
+  }
+  advance_step(a.step, par, n, blk == 0);
+}
+
+template <int M, int FLUX, int S>
+__global__ __launch_bounds__(kEulerBlock) void euler_step_kernel(EulerArgs a) {
+  __shared__ double lds[(kEulerBlock / 64) * fat_wave_doubles<S>()];
+  euler_step_body<M, FLUX, S>(a, a.ws, a.wout, lds, xcd_item(blockIdx.x, gridDim.x), a.step[a.par], a.par);
+}
+
+// ---------------------------------------------------------------- stage kernel (limiter)
 
 // Wavefront-local stage kernel.  Lane l of a wavefront holds element
 // base + l - H (base = (64 - 2H) * wavefront index, H = 1, or 2 with the
@@ -449,11 +625,11 @@ __device__ __forceinline__ void gather_first_slots(const EulerArgs &a, int nmod,
 // element's unlimited output (bitwise the value its owner forms), the wavefront
 // stages its outputs in LDS (ls, 5M x 64 doubles per wavefront), and each owned
 // element runs the indicator and, if troubled, the WENO reconstruction from them.
-template <int M, int FLUX, bool LIM>
+template <int M, int FLUX>
 __device__ __forceinline__ void euler_stage_body(const EulerArgs &a, const LimiterArgs &l, double *lds, int *rounds,
                                                  int blk, int par) {
   constexpr int V = 5, Q = M;
-  constexpr int H = LIM ? 2 : 1;
+  constexpr int H = 2;
   constexpr int WE = 64 - 2 * H;
   const int lane = threadIdx.x & 63;
   const int base = ((blk * kEulerBlock + threadIdx.x) >> 6) * WE;
@@ -465,8 +641,8 @@ __device__ __forceinline__ void euler_stage_body(const EulerArgs &a, const Limit
   const bool ghost_r = !a.periodic && xu == E;
   // loaded: owned elements and H neighbours on each side (wrapped), never past a transmissive end
   const bool loads = live && (a.periodic ? xu <= E - 1 + H : (xu >= 0 && xu < E));
-  // forms an output: owned, and with the limiter the first neighbour on each side
-  const bool calc = LIM ? live && lane >= 1 && lane <= 62 && (a.periodic ? xu <= E : (xu >= 0 && xu < E)) : own;
+  // forms an output: owned, and the first neighbour on each side
+  const bool calc = live && lane >= 1 && lane <= 62 && (a.periodic ? xu <= E : (xu >= 0 && xu < E));
   // computes the flux at face xu + 1 (faces 0..E; periodic faces wrap)
   const bool face_lane = live && lane <= 62 && (a.periodic ? xu + 1 <= E - 1 + H : (xu >= -1 && xu < E));
   int x = xu;   // within a few periods of [0, E)
@@ -482,7 +658,7 @@ __device__ __forceinline__ void euler_stage_body(const EulerArgs &a, const Limit
   bool ok = true;
   const double *w0 = a.w0, *ws = a.ws;
   double *wout = a.wout;
-  if (LIM && a.alt) {
+  if (a.alt) {
     const int c = (int)(n & 1);
     w0 = a.W[c];
     ws = a.stage == 0 ? a.W[c] : a.stage == 1 ? a.W[1 - c] : a.W[2];
@@ -509,19 +685,19 @@ __device__ __forceinline__ void euler_stage_body(const EulerArgs &a, const Limit
   // loads are in flight
   // (the limiter kernel draws with the branch-free count, measured 0.9 us faster per stage on
   // the shock workload; the plain kernel with the ordered search, 0.6 us faster on the smooth one)
-  const int kf = iface >= 0 ? eff_delay<LIM>(a.dl, n, iface) : 0;
+  const int kf = iface >= 0 ? eff_delay<true>(a.dl, n, iface) : 0;
   double Fat[V];
-  if (kf > 0) at_flux(a, nmod, iface, kf, Fat);
+  if (kf > 0) at_flux(a, nmod, a.stage, iface, kf, Fat);
 
   // with the limiter: this wavefront's outputs, [component][lane], and the neighbour
   // sources of the owned elements.  Faces at a transmissive end or a delayed PE interface
   // need a slot: kSlotLanes such elements per round, two slots each; the first round's AT
   // neighbours are gathered now, while the state loads are in flight.
-  double *ls = LIM ? lds + (threadIdx.x >> 6) * lds_wave_doubles<M>() : nullptr;
+  double *ls = lds + (threadIdx.x >> 6) * lds_wave_doubles<M>();
   NbSide sd[2];
   bool needs = false;
   unsigned long long nball = 0;
-  if constexpr (LIM) {
+  {
     // an owned element's faces x and x + 1 are the faces of the previous lane and of this one
     const int iface_prev = dpp_move<kDppFromPrev>(iface);
 #pragma unroll
@@ -621,15 +797,14 @@ __device__ __forceinline__ void euler_stage_body(const EulerArgs &a, const Limit
           const double y = fma(a.dt, L, u[v][j]);
           o = use_prev ? fma(a.rk.ca, wn[v][j], a.rk.cb * y) : y;
         }
-        if (LIM) ls[(v * M + j) * 64 + lane] = o;   // stored below, limited if troubled
-        else if (own) wout[gi] = o;
+        ls[(v * M + j) * 64 + lane] = o;   // stored below, limited if troubled
         if (recR) recR[v * M + j] = o;
         if (recL) recL[v * M + j] = o;
       }
     }
   }
 
-  if constexpr (LIM) {
+  {
     const int rank = __popcll(nball & ((1ull << lane) - 1ull));
     const int my_round = needs ? rank / kSlotLanes : 0;
     // the first round's ghost slots and slot pointers are set before the barrier: they need
@@ -697,23 +872,34 @@ __device__ __forceinline__ void euler_stage_body(const EulerArgs &a, const Limit
 }
 
 template <int M, int FLUX>
-__global__ __launch_bounds__(kEulerBlock) void euler_stage_kernel(EulerArgs a) {
-  euler_stage_body<M, FLUX, false>(a, LimiterArgs{}, nullptr, nullptr, blockIdx.x, a.par);
-}
-
-template <int M, int FLUX>
 __global__ __launch_bounds__(kEulerBlock, M <= 4 ? 3 : 2) void euler_lim_kernel(EulerArgs a, LimiterArgs l) {
   __shared__ double lds[(kEulerBlock / 64) * lds_wave_doubles<M>()];
   __shared__ int rounds[kEulerBlock / 64];
-  euler_stage_body<M, FLUX, true>(a, l, lds, rounds, blockIdx.x, a.par);
+  euler_stage_body<M, FLUX>(a, l, lds, rounds, blockIdx.x, a.par);
 }
 
-// Batched stage kernel: one workgroup per (instance, block) entry of the work
-// list, for instances of one order, flux and limiter choice, all at step counter
-// parity par; an instance whose step count has reached its target is skipped by
-// all of its workgroups alike (its first one carries the count over to the
-// other parity at the step's last stage).
-template <int M, int FLUX, bool LIM>
+// Batched kernels: one workgroup per (instance, block) entry of the work list, for
+// instances of one order, flux and limiter choice, all at step counter parity par:
+// a whole step per launch without the limiter, one stage with it.  An instance whose
+// step count has reached its target is skipped by all of its workgroups alike (its
+// first one carries the count over to the other parity at the step's last launch).
+// w^n of a step lives in W[n mod 2].
+template <int M, int FLUX>
+__global__ __launch_bounds__(kEulerBlock) void euler_batch_step_kernel(const EulerSet *__restrict__ sets,
+                                                                  const int2 *__restrict__ tiles, int par) {
+  __shared__ double lds[(kEulerBlock / 64) * fat_wave_doubles<3>()];
+  const int2 tl = tiles[blockIdx.x];
+  const EulerArgs &a = sets[tl.x].st[0];
+  const long long n = a.step[par];
+  if (n >= a.target) {
+    if (tl.y == 0 && threadIdx.x == 0) a.step[par ^ 1] = n;
+    return;
+  }
+  const int c = (int)(n & 1);
+  euler_step_body<M, FLUX, 3>(a, a.W[c], a.W[1 - c], lds, tl.y, n, par);
+}
+
+template <int M, int FLUX>
 __global__ __launch_bounds__(kEulerBlock, M <= 4 ? 3 : 2) void euler_batch_kernel(const EulerSet *__restrict__ sets,
                                                                   const int2 *__restrict__ tiles, int stage,
                                                                   int par) {
@@ -724,13 +910,9 @@ __global__ __launch_bounds__(kEulerBlock, M <= 4 ? 3 : 2) void euler_batch_kerne
     if (a.advance && tl.y == 0 && threadIdx.x == 0) a.step[par ^ 1] = n;
     return;
   }
-  if constexpr (LIM) {
-    __shared__ double lds[(kEulerBlock / 64) * lds_wave_doubles<M>()];
-    __shared__ int rounds[kEulerBlock / 64];
-    euler_stage_body<M, FLUX, true>(a, sets[tl.x].lim, lds, rounds, tl.y, par);
-  } else {
-    euler_stage_body<M, FLUX, false>(a, sets[tl.x].lim, nullptr, nullptr, tl.y, par);
-  }
+  __shared__ double lds[(kEulerBlock / 64) * lds_wave_doubles<M>()];
+  __shared__ int rounds[kEulerBlock / 64];
+  euler_stage_body<M, FLUX>(a, sets[tl.x].lim, lds, rounds, tl.y, par);
 }
 
 // caller layout [E][VM] <-> device layout (sidx)
@@ -749,44 +931,65 @@ __global__ void from_planes_kernel(const double *__restrict__ src, double *__res
 
 // ---------------------------------------------------------------- launchers
 
+template <int M, int S>
+static void step_MS(int flux, const EulerArgs &a, int blocks, hipStream_t s) {
+  if (flux == 1) hipLaunchKernelGGL((euler_step_kernel<M, 1, S>), dim3(blocks), dim3(kEulerBlock), 0, s, a);
+  else hipLaunchKernelGGL((euler_step_kernel<M, 0, S>), dim3(blocks), dim3(kEulerBlock), 0, s, a);
+}
+
 template <int M>
-static hipError_t stage_M(int flux, const EulerArgs &a, const LimiterArgs *lim, hipStream_t s) {
-  const int blocks = euler_blocks(a.E, lim != nullptr);
-  if (lim) {
-    if (flux == 1) hipLaunchKernelGGL((euler_lim_kernel<M, 1>), dim3(blocks), dim3(kEulerBlock), 0, s, a, *lim);
-    else hipLaunchKernelGGL((euler_lim_kernel<M, 0>), dim3(blocks), dim3(kEulerBlock), 0, s, a, *lim);
-  } else {
-    if (flux == 1) hipLaunchKernelGGL((euler_stage_kernel<M, 1>), dim3(blocks), dim3(kEulerBlock), 0, s, a);
-    else hipLaunchKernelGGL((euler_stage_kernel<M, 0>), dim3(blocks), dim3(kEulerBlock), 0, s, a);
-  }
+static hipError_t step_M(int flux, int stages, const EulerArgs &a, hipStream_t s) {
+  const int blocks = euler_blocks(a.E, 64 - 2 * stages);
+  if (stages == 3) step_MS<M, 3>(flux, a, blocks, s);
+  else if (stages == 2) step_MS<M, 2>(flux, a, blocks, s);
+  else if (stages == 5) step_MS<M, 5>(flux, a, blocks, s);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_euler_stage(int M, int flux, const EulerArgs &a, const LimiterArgs *lim, hipStream_t s) {
+hipError_t launch_euler_step(int M, int flux, int stages, const EulerArgs &a, hipStream_t s) {
   switch (M) {
-    case 2: return stage_M<2>(flux, a, lim, s);
-    case 3: return stage_M<3>(flux, a, lim, s);
-    case 4: return stage_M<4>(flux, a, lim, s);
-    case 5: return stage_M<5>(flux, a, lim, s);
+    case 2: return step_M<2>(flux, stages, a, s);
+    case 3: return step_M<3>(flux, stages, a, s);
+    case 4: return step_M<4>(flux, stages, a, s);
+    case 5: return step_M<5>(flux, stages, a, s);
   }
   return hipErrorInvalidValue;
 }
 
-template <int M, bool LIM>
-static hipError_t batch_ML(int flux, const EulerSet *sets, const int2 *tiles, int ntiles, int stage, int par,
+template <int M>
+static hipError_t lim_M(int flux, const EulerArgs &a, const LimiterArgs &lim, hipStream_t s) {
+  const int blocks = euler_blocks(a.E, kEulerLimOwned);
+  if (flux == 1) hipLaunchKernelGGL((euler_lim_kernel<M, 1>), dim3(blocks), dim3(kEulerBlock), 0, s, a, lim);
+  else hipLaunchKernelGGL((euler_lim_kernel<M, 0>), dim3(blocks), dim3(kEulerBlock), 0, s, a, lim);
+  return hipGetLastError();
+}
+
+hipError_t launch_euler_lim(int M, int flux, const EulerArgs &a, const LimiterArgs &lim, hipStream_t s) {
+  switch (M) {
+    case 2: return lim_M<2>(flux, a, lim, s);
+    case 3: return lim_M<3>(flux, a, lim, s);
+    case 4: return lim_M<4>(flux, a, lim, s);
+    case 5: return lim_M<5>(flux, a, lim, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <int M, int FLUX>
+static hipError_t batch_MF(bool lim, const EulerSet *sets, const int2 *tiles, int ntiles, int stage, int par,
                            hipStream_t s) {
-  if (flux == 1)
-    hipLaunchKernelGGL((euler_batch_kernel<M, 1, LIM>), dim3(ntiles), dim3(kEulerBlock), 0, s, sets, tiles, stage, par);
+  if (lim)
+    hipLaunchKernelGGL((euler_batch_kernel<M, FLUX>), dim3(ntiles), dim3(kEulerBlock), 0, s, sets, tiles, stage, par);
   else
-    hipLaunchKernelGGL((euler_batch_kernel<M, 0, LIM>), dim3(ntiles), dim3(kEulerBlock), 0, s, sets, tiles, stage, par);
+    hipLaunchKernelGGL((euler_batch_step_kernel<M, FLUX>), dim3(ntiles), dim3(kEulerBlock), 0, s, sets, tiles, par);
   return hipGetLastError();
 }
 
 template <int M>
 static hipError_t batch_M(int flux, bool lim, const EulerSet *sets, const int2 *tiles, int ntiles, int stage,
                           int par, hipStream_t s) {
-  return lim ? batch_ML<M, true>(flux, sets, tiles, ntiles, stage, par, s)
-             : batch_ML<M, false>(flux, sets, tiles, ntiles, stage, par, s);
+  return flux == 1 ? batch_MF<M, 1>(lim, sets, tiles, ntiles, stage, par, s)
+                   : batch_MF<M, 0>(lim, sets, tiles, ntiles, stage, par, s);
 }
 
 hipError_t launch_euler_batch(int M, int flux, bool lim, const EulerSet *sets, const int2 *tiles, int ntiles,

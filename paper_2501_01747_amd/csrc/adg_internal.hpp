@@ -101,14 +101,14 @@ __host__ __device__ inline RkStage rk_stage(int rk, int s) {
     r.ca = s == 0 ? 0.0 : -1.0;
     r.cb = s == 0 ? 1.0 : 0.5;
   } else {
-    const double A[5] = {0.0, -567301805773.0 / 1357537059087.0, -2404267990393.0 / 2016746695238.0,
-                         -3550918686646.0 / 2091501179385.0, -1275806237668.0 / 842570457699.0};
-    const double B[5] = {1432997174477.0 / 9575080441755.0, 5161836677717.0 / 13612068292357.0,
-                         1720146321549.0 / 2090206949498.0, 3134564353537.0 / 4481467310338.0,
-                         2277821191437.0 / 14882151754819.0};
+    // nested selections, not an indexed table: a kernel that loops over the stages would keep
+    // the table in scratch memory
     r.two_n = 1;
-    r.ca = A[s];
-    r.cb = B[s];
+    r.ca = s == 0 ? 0.0 : s == 1 ? -567301805773.0 / 1357537059087.0 : s == 2 ? -2404267990393.0 / 2016746695238.0
+           : s == 3 ? -3550918686646.0 / 2091501179385.0 : -1275806237668.0 / 842570457699.0;
+    r.cb = s == 0 ? 1432997174477.0 / 9575080441755.0 : s == 1 ? 5161836677717.0 / 13612068292357.0
+           : s == 2 ? 1720146321549.0 / 2090206949498.0 : s == 3 ? 3134564353537.0 / 4481467310338.0
+           : 2277821191437.0 / 14882151754819.0;
   }
   return r;
 }
@@ -132,10 +132,10 @@ struct EulerArgs {
   RkStage rk;
   double *kbuf;         // 2N register read by this stage (2N schemes)
   double *kout;         // 2N register written by this stage (kbuf itself without the limiter)
-  // batched Shu-Osher stages with the limiter: w^n lives in W[n mod 2] (n = the step
-  // counter), stage 1 writes W[1 - n mod 2], stage 2 W[2], stage 3 W[1 - n mod 2], so
-  // no stage writes a buffer it reads (the kernel then ignores w0, ws and wout; the
-  // single-problem solver passes the same buffers explicitly)
+  // batched Shu-Osher steps: w^n lives in W[n mod 2] (n = the step counter) and the step
+  // ends in W[1 - n mod 2]; with the limiter stage 1 writes W[1 - n mod 2], stage 2 W[2],
+  // stage 3 W[1 - n mod 2].  No launch writes a buffer it reads (the kernels then ignore w0,
+  // ws and wout; the single-problem solver passes the same buffers explicitly)
   int alt;
   double *W[3];
   int store_U;          // publish boundary-element outputs for the limiter
@@ -184,19 +184,22 @@ struct EulerSet {
 };
 
 // Kernel launchers (defined in the .hip files).
-// One stage of the one-step model; `lim` (null = no limiter) adds the limiter to
-// the same kernel.
-hipError_t launch_euler_stage(int M, int flux, const EulerArgs &a, const LimiterArgs *lim, hipStream_t s);
-// Batched one-step stage over a work list of (instance, block) entries, all of
-// order M, flux `flux` (Rusanov/HLLC) and limiter choice `lim`, at step counter
-// parity `par`.
+// One whole time step (`stages` = 3, 2 or 5 RK stages) of the one-step model without the
+// limiter: reads a.ws, writes a.wout (another buffer).
+hipError_t launch_euler_step(int M, int flux, int stages, const EulerArgs &a, hipStream_t s);
+// One stage of the one-step model with the limiter in the same kernel.
+hipError_t launch_euler_lim(int M, int flux, const EulerArgs &a, const LimiterArgs &lim, hipStream_t s);
+// Batched one-step launch over a work list of (instance, block) entries, all of order M,
+// flux `flux` (Rusanov/HLLC) and limiter choice `lim`, at step counter parity `par`: one
+// stage with the limiter, the whole step (`stage` ignored) without.
 hipError_t launch_euler_batch(int M, int flux, bool lim, const EulerSet *sets, const int2 *tiles, int ntiles,
                               int stage, int par, hipStream_t s);
-// Workgroups of the one-step stage kernel for E elements: a wavefront owns 62
-// elements, 60 with the limiter (two halo lanes on each side).
-__host__ __device__ inline int euler_blocks(int E, bool lim) {
-  const int we = lim ? 60 : 62;
-  const int waves = (E + we - 1) / we;
+// Elements a wavefront owns: 64 lanes less the halo on each side (two lanes with the limiter,
+// one per stage of the step without).
+constexpr int kEulerLimOwned = 60, kEulerStepOwned = 58;   // SSP-RK3 (batches)
+// Workgroups for E elements with `owned` elements per wavefront.
+__host__ __device__ inline int euler_blocks(int E, int owned) {
+  const int waves = (E + owned - 1) / owned;
   return (waves + kEulerBlock / 64 - 1) / (kEulerBlock / 64);
 }
 hipError_t launch_to_planes(const double *src, double *dst, int E, int VM, hipStream_t s);

@@ -315,7 +315,7 @@ adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc
     a.store_U = disc->limiter && L.nif > 0;
     a.kbuf = P.W[2];
     a.kout = P.W[2];
-    a.alt = disc->limiter && !rk_stage(disc->rk, 0).two_n;
+    a.alt = !rk_stage(disc->rk, 0).two_n;
     for (int b = 0; b < 3; ++b) a.W[b] = P.W[b];
     a.rk = rk_stage(disc->rk, 0);
     a.dt = disc->dt;

@@ -1,0 +1,43 @@
+"""The one-step model's whole-step kernel at the edges of its wavefront tiles (64 lanes less a halo
+of one lane per RK stage on each side: 58 owned elements for SSP-RK3, 60 for RK2, 54 for the
+five-stage scheme), against the oracle at the repository's parity bound (1e-10)."""
+import pytest
+
+from _parity import check
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def adg():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2501_01747_amd import adg as lib
+
+    return lib
+
+
+OWNED = {"ssprk3": 58, "rk2": 60, "lserk4": 54}
+# meshes shorter than the halo, and around one wavefront and one workgroup of four
+SIZES = {rk: [1, 2, 4, n - 1, n, n + 1, 4 * n - 1, 4 * n + 1] for rk, n in OWNED.items()}
+
+
+@pytest.mark.parametrize("bc,flux", [("periodic", "rusanov"), ("transmissive", "hllc")])
+@pytest.mark.parametrize("rk,E", [(rk, E) for rk, sizes in SIZES.items() for E in sizes])
+def test_whole_step_tiles(adg, orc, rk, E, bc, flux):
+    """Every element its own PE on the short meshes (every face delayed), five PEs on the others."""
+    order_p = 1 + E % 4
+    case, w0 = gen.case_c0(E=E, order_p=order_p, n_pe=min(E, 5), mode="saa", pmf=(0.3, 0.4, 0.3),
+                           cfl={1: 0.1, 2: 0.08, 3: 0.04, 4: 0.01}[order_p])
+    case["disc"].update(bc=bc, flux=flux, rk=rk)
+    s = adg.Solver(case)
+    s.set_state(w0)
+    o = orc.OracleSolver(case, w0, 13)
+    s.step(12)
+    o.step(12)
+    check(s.state(), o.state(), case, 1e-10, f"{rk} E={E} {bc}")
+    assert s.step_count() == 12
+    s.close()
