@@ -244,8 +244,8 @@ def build_c3_batch(precision: str, n_inst: int = 4096):
 
 
 def batch_decompositions(steps: int, precision: str):
-    """Time every work decomposition of the batched kernel on the batched workload (the
-    autotuner's candidates): HIP events over `steps` plain steps each, after one untimed step."""
+    """Time the batched kernel on the batched workload under both decomposition numbers (one kernel):
+    HIP events over `steps` plain steps each, after one untimed step."""
     import torch
 
     b, cases = build_c3_batch(precision)
@@ -260,7 +260,7 @@ def batch_decompositions(steps: int, precision: str):
         ev1.record(b.stream)
         torch.cuda.synchronize()
         out[cfg] = ev0.elapsed_time(ev1) / (3 * steps)
-        print(json.dumps({"decomposition": cfg, "tile_elems": (8, 4)[cfg], "launch_ms": out[cfg]}), flush=True)
+        print(json.dumps({"decomposition": cfg, "stage_ms": out[cfg]}), flush=True)
     b.close()
     return out
 
@@ -276,7 +276,6 @@ def bench_batched(steps: int, warmup: int, graph: int, precision: str = "mixed",
 
     b, cases = build_c3_batch(precision, n_inst)
     elems = sum(c["disc"]["n_elem"] for c, _ in cases)
-    tuned = b.autotune()
     graph = min(graph, steps)   # the timed steps: steps // graph replays, steps mod graph plain steps
     if graph:
         b.set_graph(graph)
@@ -291,8 +290,9 @@ def bench_batched(steps: int, warmup: int, graph: int, precision: str = "mixed",
     el = time.perf_counter() - t0
     st, er = b.poll()
     dof = sum(gen.dof(c) for c, _ in cases)
-    # every instance is a detailed-chemistry one: a step is three launches of the batched
-    # kernel, timed with HIP events over the timed region on the batch's stream
+    # every instance is a detailed-chemistry one: a step is three stages of the batched kernel
+    # (two chains of launches side by side), timed with HIP events over the timed region on the
+    # batch's stream; launch_ms is a stage of all instances
     stage_ms = ev0.elapsed_time(ev1) / (3 * steps)
     flops = sum(detailed_stage_flops(c) for c, _ in cases)
     achieved = flops / (stage_ms * 1e-3) / 1e12
@@ -302,11 +302,11 @@ def bench_batched(steps: int, warmup: int, graph: int, precision: str = "mixed",
         "steps": steps, "warmup": warmup, "precision": precision,
         "config": {"workload": "c3_batched_ignition", "instances": len(cases), "elements": elems, "dof": dof,
                    "order_p": [2, 3], "graph_steps": graph,
-                   "timed_graph_replays": steps // graph if graph else 0, "tile_elems": (8, 4)[tuned]},
+                   "timed_graph_replays": steps // graph if graph else 0},
         "state_errors": int(er.sum()), "steps_done_min": int(st[st >= 0].min()),
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_VECTOR_PEAK_TFLOPS,
-                     "traffic": read_traffic("c3", ["adg_ns.hip", "adg_ns.hpp"]), "kernel": "ns_batch_kernel",
+                     "traffic": read_traffic("c3", ["adg_ns_lane.hip", "adg_ns.hpp"]), "kernel": "ns_lane_batch_kernel",
                      "launch_ms": stage_ms, "flops_per_launch": flops},
     }
     if cpu:

@@ -129,8 +129,10 @@ typedef struct {
                              fluxes, source projection and RK update in FP64.  Applied for N_p <= 3,
                              where the error against the FP64 solution stays below a tenth of the
                              discretisation error (4 % of it measured at N_p = 3); N_p = 4 keeps FP64
-                             operators (FP32 measured 11 times the discretisation error there).  The
-                             one-step model returns ADG_ERR_UNSUPPORTED.
+                             operators (FP32 measured 11 times the discretisation error there), and
+                             so does the kernel of batches and large problems, where FP32 operators
+                             cost their conversions and gain nothing.  The one-step model returns
+                             ADG_ERR_UNSUPPORTED.
                              ADG_MIXED_BF16: ADG_ERR_UNSUPPORTED: BF16 (8-bit significand) operators
                              would raise the FP32 path's operator error by about 2^16, past the
                              discretisation error at every order of these workloads.
@@ -220,7 +222,8 @@ adg_status adg_set_graph(adg_solver *s, int32_t steps_per_graph);
    null solver): with adg_set_graph(g), adg_step(n) adds n / g. */
 int64_t adg_graph_replays(const adg_solver *s);
 
-/* Choose the stage kernel's work decomposition by measurement: for the
+/* Choose the stage kernel's work decomposition by measurement (without it, one is
+   chosen by the problem's size): for the
    detailed-chemistry model, the tile size (4 or 8 elements) and workgroup size
    (256, 512 or 1024 threads) of the stage kernel: every candidate is warmed up,
    then timed over n_reps launches of the first RK stage on the current state in
@@ -229,8 +232,9 @@ int64_t adg_graph_replays(const adg_solver *s);
    more than 3 %.  The timed launches only rewrite the first stage buffer and the
    current level's first-stage history, which the next step recomputes, so the
    solution is unchanged.  *choice (optional) receives the chosen candidate
-   (0: 8/512, 1: 8/256, 2: 4/256, 3: 4/512, 4: 8/1024; always 0 for the one-step model,
-   whose kernel has one decomposition).  Synchronises. */
+   (0: 8/512, 1: 8/256, or for more than 8192 elements (12288 with more than 9 species)
+   the kernel with one lane per point, 2: 4/256, 3: 4/512, 4: 8/1024; always 0 for the
+   one-step model, whose kernel has one decomposition).  Synchronises. */
 adg_status adg_autotune(adg_solver *s, int32_t n_reps, int32_t *choice);
 
 /* Use work decomposition `config` (the numbering of adg_autotune; only 0 for
@@ -268,8 +272,8 @@ adg_status adg_create_noalloc(const adg_physics *phys, const adg_discretization 
  * Batches of independent instances in one workspace.
  *
  * Many ADG problems of different sizes, orders, PE layouts and delay models
- * advance together: every RK stage of a time step is one batched launch for
- * all detailed-chemistry instances (plus one per order, flux and limiter
+ * advance together: every RK stage of a time step is one or two batched launches
+ * for all detailed-chemistry instances (plus one per order, flux and limiter
  * choice for the one-step model), so small
  * instances fill the device together.  Each workgroup works on one instance
  * with that instance's own arguments: an instance's result does not depend on
@@ -342,27 +346,24 @@ adg_status adg_batch_set_graph(adg_batch *b, int32_t steps_per_graph);
 adg_status adg_batch_profile(adg_batch *b, int32_t n_steps, double *ms_out, int64_t *launches_out,
                              int32_t n_classes);
 
-/* Choose the tile size (8 or 4 elements) of the batched detailed-chemistry
-   kernel by timing n_reps launches of its first RK stage for the current batch
-   (state unchanged, as for adg_autotune; three interleaved rounds, each
-   candidate's fastest counting); kept until the next call.  *choice
-   (optional): 0 = 8 elements, 1 = 4.  Synchronises. */
+/* The batched detailed-chemistry kernel has one work decomposition, so there is
+   nothing to time: prepares the work list for the current batch and returns
+   0 in *choice (optional).  Synchronises if the composition changed. */
 adg_status adg_batch_autotune(adg_batch *b, int32_t n_reps, int32_t *choice);
 
-/* Use work decomposition `config` of the batched detailed-chemistry kernel
-   (adg_batch_autotune's numbering, 0 or 1; ADG_ERR_ARG otherwise) from the next
-   step on.  Results do not depend on it beyond the order of floating-point sums. */
+/* Accepts 0 or 1 (ADG_ERR_ARG otherwise); both name the batched
+   detailed-chemistry kernel's one work decomposition. */
 adg_status adg_batch_set_kernel_config(adg_batch *b, int32_t config);
 
-/* Spread each RK stage's launches (one per group: the detailed-chemistry
-   instances, and one per (order, flux, limiter) class of one-step instances)
-   over `streams` streams (1..4; ADG_ERR_ARG otherwise): the batch's stream and
-   up to three more of the default priority, created by the library on first
-   use and joined back into the batch's stream before the next stage.  Groups
-   touch disjoint instances, so results do not depend on it; with several
-   groups the smaller launches overlap the larger ones instead of waiting for
-   them.  Default 4; 1 launches everything on the batch's stream.  A captured
-   graph is re-captured at the next step. */
+/* Spread the launches of a step's groups (the detailed-chemistry instances in
+   one or two groups, and one group per (order, flux, limiter) class of one-step
+   instances) over `streams` streams (1..4; ADG_ERR_ARG otherwise): the batch's
+   stream and up to three more of the default priority, created by the library on
+   first use, forked from the batch's stream at the start of a call and joined
+   back into it at its end.  Groups touch disjoint instances, so each runs its own
+   chain of stages and results do not depend on it; the smaller launches overlap
+   the larger ones instead of waiting for them.  Default 4; 1 launches everything
+   on the batch's stream.  A captured graph is re-captured at the next step. */
 adg_status adg_batch_set_group_streams(adg_batch *b, int32_t streams);
 
 /* Number of admitted instances. */

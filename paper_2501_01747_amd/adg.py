@@ -402,17 +402,17 @@ class Batch:
         self._check(adg_batch_set_graph(self.h, int(steps_per_graph)))
 
     def autotune(self, n_reps: int = 5) -> int:
-        """Pick the batched kernel's tile size by timing (state unchanged)."""
+        """Prepare the work list (the batched kernel has one decomposition: returns 0)."""
         c = C.c_int32(0)
         self._check(adg_batch_autotune(self.h, int(n_reps), C.byref(c)))
         return c.value
 
     def set_decomposition(self, config: int):
-        """Use the batched kernel's work decomposition `config` (autotune's numbering)."""
+        """Accepts 0 or 1: the batched kernel has one decomposition."""
         self._check(adg_batch_set_kernel_config(self.h, int(config)))
 
     def set_group_streams(self, streams: int):
-        """Spread each stage's group launches over `streams` streams (1..4)."""
+        """Spread the groups' launches over `streams` streams (1..4)."""
         self._check(adg_batch_set_group_streams(self.h, int(streams)))
 
     def profile(self, n_steps: int) -> dict:

@@ -40,7 +40,8 @@ struct adg_solver {
   // so every alignment has a graph and no realigning plain step is ever needed.
   int graph_cur[2] = {0, 0}, graph_cur_after[2] = {0, 0};
   int graph_par[2] = {0, 0}, graph_par_after[2] = {0, 0};
-  int ns_cfg = 0;   // work decomposition of the detailed-chemistry stage kernel
+  int ns_cfg = -1;  // work decomposition of the detailed-chemistry stage kernel (-1: none chosen)
+  bool at_ready = false;   // the last launch left its successor's AT combinations (set_at_buffers)
   int graph_steps = 0;
   int graph_built_for = 0;
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -86,14 +87,19 @@ adg_status hip_fail(adg_solver *s, hipError_t e, const char *where) {
 // pair around each launch for adg_profile.
 typedef void (*TimerFn)(adg_solver *, int cls, bool begin);
 
+int ns_kernel(const adg_solver *s, int cfg) {
+  return ns_kernel_of(cfg, s->P.lay.E, s->P.lay.M, s->P.phys.n_species);
+}
+
 // Carried AT combinations of the launch of `stage` in the step at parity s->par: launch number
 // n S + stage of the run (n mod 2 = s->par: both start at zero) reads buffer (n S + stage) mod 2
-// and leaves its successor's values in the other one.  After a reset no delay is positive before
-// step q, so no launch reads a buffer before one has been written for it.
+// and leaves its successor's values in the other one.  The lane-per-point kernels neither read nor
+// write them, so a launch reads them only if its predecessor wrote them (s->at_ready); it forms
+// the same values from the history otherwise.
 void set_at_buffers(const adg_solver *s, NsArgs &a, int stage) {
   if (!s->P.at) return;
   const int b = (s->par * s->P.lay.S + stage) & 1;
-  a.at_in = s->P.at + (size_t)b * s->P.at_stride;
+  a.at_in = s->at_ready ? s->P.at + (size_t)b * s->P.at_stride : nullptr;
   a.at_out = s->P.at + (size_t)(1 - b) * s->P.at_stride;
 }
 
@@ -166,7 +172,9 @@ adg_status enqueue_step(adg_solver *s, hipStream_t st, TimerFn timer) {
       a.par = s->par;
       set_at_buffers(s, a, stage);
       if (timer) timer(s, 0, true);
-      HIP_TRY(s, launch_ns_stage(M, s->ns_cfg, a, s->P.disc.precision == ADG_MIXED_FP32, st));
+      const int kernel = ns_kernel(s, s->ns_cfg);
+      HIP_TRY(s, launch_ns_stage(M, kernel, a, s->P.disc.precision == ADG_MIXED_FP32, st));
+      s->at_ready = kernel != kNsLane;
       if (timer) timer(s, 0, false);
     }
   }
@@ -187,8 +195,10 @@ void destroy_graph(adg_solver *s) {
 // Capture graph k from alignment (cur0, par0); nothing runs, the capture only records.
 adg_status capture_graph(adg_solver *s, int k, int cur0, int par0) {
   const int cur_keep = s->cur, par_keep = s->par;
+  const bool at_keep = s->at_ready;
   s->cur = cur0;
   s->par = par0;
+  s->at_ready = false;   // whatever ran before a replay: its first launch reads no carried values
   HIP_TRY(s, hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
   adg_status rc = ADG_OK;
   for (int i = 0; i < s->graph_steps && rc == ADG_OK; ++i) rc = enqueue_step(s, s->cap_stream, nullptr);
@@ -198,6 +208,7 @@ adg_status capture_graph(adg_solver *s, int k, int cur0, int par0) {
   s->graph_par_after[k] = s->par;
   s->cur = cur_keep;
   s->par = par_keep;
+  s->at_ready = at_keep;
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(s->cap_stream, &g);
   if (rc != ADG_OK) { if (g) (void)hipGraphDestroy(g); return rc; }
@@ -297,6 +308,7 @@ adg_status adg_set_state(adg_solver *s, const double *w, int64_t count, int32_t 
   }
   s->cur = 0;
   s->par = 0;
+  s->at_ready = false;
   s->graph_replays = 0;
   HIP_TRY(s, reset_problem(s->P, s->stream));
   if (where == ADG_HOST) HIP_TRY(s, hipStreamSynchronize(s->stream));
@@ -320,6 +332,7 @@ adg_status adg_step(adg_solver *s, int32_t n_steps) {
         HIP_TRY(s, hipGraphLaunch(s->gexec[k], s->stream));
         s->cur = s->graph_cur_after[k];
         s->par = s->graph_par_after[k];
+        s->at_ready = ns_kernel(s, s->ns_cfg) != kNsLane;
         left -= s->graph_steps;
         s->graph_replays += 1;
       } else {
@@ -448,13 +461,13 @@ adg_status adg_autotune(adg_solver *s, int32_t n_reps, int32_t *choice) {
   HIP_TRY(s, hipEventCreate(&e0));
   HIP_TRY(s, hipEventCreate(&e1));
   for (int c = 0; c < kNsConfigs; ++c) {
-    for (int r = 0; r < 2; ++r) HIP_TRY(s, launch_ns_stage(M, c, a, mixed, s->stream));
+    for (int r = 0; r < 2; ++r) HIP_TRY(s, launch_ns_stage(M, ns_kernel(s, c), a, mixed, s->stream));
     t[c] = 1e30;
   }
   for (int round = 0; round < 3; ++round)
     for (int c = 0; c < kNsConfigs; ++c) {
       HIP_TRY(s, hipEventRecord(e0, s->stream));
-      for (int r = 0; r < n_reps; ++r) HIP_TRY(s, launch_ns_stage(M, c, a, mixed, s->stream));
+      for (int r = 0; r < n_reps; ++r) HIP_TRY(s, launch_ns_stage(M, ns_kernel(s, c), a, mixed, s->stream));
       HIP_TRY(s, hipEventRecord(e1, s->stream));
       HIP_TRY(s, hipEventSynchronize(e1));
       float ms = 0.0f;

@@ -7,8 +7,7 @@
 // refused with ADG_ERR_NOMEM: admission is by device-memory footprint.
 //
 // A time step launches, per stage, one batched kernel for all detailed-
-// chemistry instances (orders dispatched inside the kernel) and one batched
-// kernel per (order, flux) group of limited one-step instances, the limiter
+// chemistry instances (orders dispatched inside the kernel) and one batched kernel per (order, flux) group of limited one-step instances, the limiter
 // inside that kernel; unlimited one-step instances take one launch per (order,
 // flux) group and step.  Every workgroup works on one instance
 // only, with that instance's own arguments, so the arithmetic of an instance
@@ -16,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstring>
 #include <map>
 #include <string>
@@ -44,6 +44,12 @@ struct Slot {
 constexpr int kBatchMechs = 16;
 
 constexpr int kGroupStreams = 4;
+// From this many tiles on (two a CU) the detailed-chemistry instances run as two chains of launches:
+// one chain's next stage fills the CUs that the other's last tiles leave idle (64 instances of 128..4096
+// elements: 56 us per stage in one chain, 45 in two, 45 in three; 1024 instances 681, 665, 657); below,
+// a second launch per stage costs more than it fills (8 instances: 19.3 in one, 21.2 in two).
+constexpr int kChains = 2;
+constexpr long long kChainTiles = 512;
 
 struct Group {
   int kind;  // 0 detailed stage, 1 one-step stage
@@ -78,7 +84,6 @@ struct adg_batch {
   long long elems = 0;
   int active = 0;
   bool dirty = true;
-  int tile_elems = 8;        // elements per tile of the detailed-chemistry kernel (4 or 8)
   std::vector<Group> groups;
   std::vector<int2> h_tiles;
   int graph_steps = 0;
@@ -88,8 +93,8 @@ struct adg_batch {
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
   hipStream_t cap_stream = nullptr;
-  // launches of a stage's groups spread over the batch's stream and up to kGroupStreams - 1
-  // extra streams (default priority), joined before the next stage; 1 = all on one stream
+  // the groups' launches spread over the batch's stream and up to kGroupStreams - 1 extra
+  // streams (default priority), joined at the end of a call; 1 = all on one stream
   int group_streams = kGroupStreams;
   hipStream_t aux[kGroupStreams - 1] = {};
   hipEvent_t fork = nullptr;
@@ -162,18 +167,22 @@ void heap_give(adg_batch *b, size_t off, size_t bytes) {
   }
 }
 
-// Work list: detailed instances first (one group), then one-step instances by
-// (order, flux, limiter).  Entries of one instance are consecutive.
+// Chains of launches that the detailed-chemistry instances are split over.
+int detailed_chains(const adg_batch *b, long long tiles) {
+  return tiles < kChainTiles ? 1 : std::min(b->group_streams, kChains);
+}
+
+// Work list: detailed instances first (by order, in as many groups as chains, of about equal tile
+// counts), then one-step instances by (order, flux, limiter).  Entries of one instance are consecutive.
 void rebuild_tiles(adg_batch *b) {
   b->groups.clear();
   b->h_tiles.clear();
-  auto add_group = [&](int kind, int M, int flux, bool lim, auto pick, auto nblocks) {
+  auto add_group = [&](int kind, int M, int flux, bool lim, const std::vector<int> &slots, auto stride) {
     Group g{kind, M, flux, lim, (int)b->h_tiles.size(), 0};
-    for (int i = 0; i < (int)b->slots.size(); ++i) {
-      const Slot &s = b->slots[i];
-      if (!s.used || !pick(s)) continue;
-      const int nb = nblocks(s);
-      for (int k = 0; k < nb; ++k) b->h_tiles.push_back(make_int2(i, k * (kind == 0 ? b->tile_elems : 1)));
+    for (int i : slots) {
+      const int E = b->slots[i].P.lay.E;
+      const int nb = kind == 0 ? (E + stride(i) - 1) / stride(i) : euler_blocks(E, lim ? kEulerLimOwned : kEulerStepOwned);
+      for (int k = 0; k < nb; ++k) b->h_tiles.push_back(make_int2(i, k * stride(i)));
     }
     g.n = (int)b->h_tiles.size() - g.off;
     // XCD-aware order: workgroup p of the launch takes work item xcd_item(p, n), so each XCD
@@ -182,23 +191,31 @@ void rebuild_tiles(adg_batch *b) {
     for (int p = 0; p < g.n; ++p) b->h_tiles[g.off + p] = run[xcd_item(p, g.n)];
     if (g.n > 0) b->groups.push_back(g);
   };
-  add_group(0, 0, 0, false, [](const Slot &s) { return s.P.phys.model == ADG_DETAILED; },
-            [&](const Slot &s) { return (s.P.lay.E + b->tile_elems - 1) / b->tile_elems; });
-  if (!b->groups.empty() && b->groups[0].kind == 0) {
-    int mm = 2;
-    for (const Slot &s : b->slots)
-      if (s.used && s.P.phys.model == ADG_DETAILED) mm = std::max(mm, s.P.lay.M);
-    b->groups[0].M = mm;
+  std::vector<int> det;
+  std::map<std::array<int, 3>, std::vector<int>> one;
+  for (int i = 0; i < (int)b->slots.size(); ++i) {
+    const Slot &s = b->slots[i];
+    if (!s.used) continue;
+    if (s.P.phys.model == ADG_DETAILED) det.push_back(i);
+    else one[{s.P.lay.M, s.P.disc.flux, s.P.disc.limiter != 0}].push_back(i);
   }
-  for (int M = 2; M <= kMaxM; ++M)
-    for (int flux = 0; flux <= 1; ++flux)
-      for (int lim = 0; lim <= 1; ++lim)
-        add_group(1, M, flux, lim != 0,
-                  [&](const Slot &s) {
-                    return s.P.phys.model == ADG_ONESTEP && s.P.lay.M == M && s.P.disc.flux == flux &&
-                           (s.P.disc.limiter != 0) == (lim != 0);
-                  },
-                  [&](const Slot &s) { return euler_blocks(s.P.lay.E, lim ? kEulerLimOwned : kEulerStepOwned); });
+  auto order = [&](int i) { return b->slots[i].P.lay.M; };
+  auto te = [&](int i) { return ns_lane_tile_elems(order(i)); };
+  auto tiles_of = [&](int i) { return (long long)((b->slots[i].P.lay.E + te(i) - 1) / te(i)); };
+  std::stable_sort(det.begin(), det.end(), [&](int x, int y) { return order(x) > order(y); });
+  long long total = 0, done = 0;
+  for (int i : det) total += tiles_of(i);
+  const int chains = detailed_chains(b, total);
+  size_t at = 0;
+  for (int c = 0; c < chains && at < det.size(); ++c) {
+    std::vector<int> part;
+    while (at < det.size() && (part.empty() || c == chains - 1 || done * chains < total * (c + 1))) {
+      part.push_back(det[at]);
+      done += tiles_of(det[at++]);
+    }
+    add_group(0, order(part.front()), 0, false, part, te);
+  }
+  for (const auto &kv : one) add_group(1, kv.first[0], kv.first[1], kv.first[2] != 0, kv.second, [](int) { return 1; });
 }
 
 // The extra streams and events of concurrent group launches, created on first use.
@@ -212,50 +229,52 @@ adg_status ensure_group_streams(adg_batch *b) {
   return ADG_OK;
 }
 
-adg_status enqueue_batch_step(adg_batch *b, hipStream_t st, bool timed) {
-  // a stage's groups touch disjoint instances: with several groups they may run side by side
-  // (group k on stream k mod S, the first on st), every stream joined back before the next stage
+// `steps` time steps on stream st (timed: an event pair around every launch, all on one stream).
+// The groups hold disjoint instances and nothing passes between them, so with several groups each
+// runs its whole chain of launches side by side with the others (group k on stream k mod S, the
+// first on st), forked from st at the start and joined back into it at the end.
+adg_status enqueue_batch_steps(adg_batch *b, hipStream_t st, int steps, bool timed) {
+  if (steps <= 0) return ADG_OK;
   const int nstreams = timed ? 1 : std::min<int>(b->group_streams, (int)b->groups.size());
   if (nstreams > 1) {
     adg_status rc = ensure_group_streams(b);
     if (rc != ADG_OK) return rc;
+    BHIP(b, hipEventRecord(b->fork, st));
+    for (int k = 1; k < nstreams; ++k) BHIP(b, hipStreamWaitEvent(b->aux[k - 1], b->fork, 0));
   }
-  for (int stage = 0; stage < 3; ++stage) {
-    if (nstreams > 1) {
-      BHIP(b, hipEventRecord(b->fork, st));
-      for (int k = 1; k < nstreams; ++k) BHIP(b, hipStreamWaitEvent(b->aux[k - 1], b->fork, 0));
-    }
-    for (int gi = 0; gi < (int)b->groups.size(); ++gi) {
-      const Group &g = b->groups[gi];
-      if (g.kind == 1 && !g.lim && stage > 0) continue;   // its whole step ran in the first launch
-      const hipStream_t gs = nstreams > 1 && gi % nstreams ? b->aux[gi % nstreams - 1] : st;
-      hipEvent_t e0 = nullptr, e1 = nullptr;
-      if (timed) {
-        BHIP(b, hipEventCreate(&e0));
-        BHIP(b, hipEventRecord(e0, st));
-      }
-      if (g.kind == 0) {
-        BHIP(b, launch_ns_batch(b->d_ns, b->d_tiles + g.off, g.n, stage, b->par, b->precision == ADG_MIXED_FP32,
-                                g.M, b->tile_elems, gs));
-      } else {
-        BHIP(b, launch_euler_batch(g.M, g.flux, g.lim, b->d_eu, b->d_tiles + g.off, g.n, stage, b->par, gs));
-      }
-      if (timed) {
-        BHIP(b, hipEventCreate(&e1));
-        BHIP(b, hipEventRecord(e1, st));
-        b->prof_events.push_back(e0);
-        b->prof_events.push_back(e1);
-        b->prof_class.push_back(g.kind);
+  for (int step = 0; step < steps; ++step) {
+    for (int stage = 0; stage < 3; ++stage) {
+      for (int gi = 0; gi < (int)b->groups.size(); ++gi) {
+        const Group &g = b->groups[gi];
+        if (g.kind == 1 && !g.lim && stage > 0) continue;   // its whole step ran in the first launch
+        const hipStream_t gs = nstreams > 1 && gi % nstreams ? b->aux[gi % nstreams - 1] : st;
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        if (timed) {
+          BHIP(b, hipEventCreate(&e0));
+          BHIP(b, hipEventRecord(e0, st));
+        }
+        if (g.kind == 0) {
+          BHIP(b, launch_ns_lane_batch(g.M, b->d_ns, b->d_tiles + g.off, g.n, stage, b->par, gs));
+        } else {
+          BHIP(b, launch_euler_batch(g.M, g.flux, g.lim, b->d_eu, b->d_tiles + g.off, g.n, stage, b->par, gs));
+        }
+        if (timed) {
+          BHIP(b, hipEventCreate(&e1));
+          BHIP(b, hipEventRecord(e1, st));
+          b->prof_events.push_back(e0);
+          b->prof_events.push_back(e1);
+          b->prof_class.push_back(g.kind);
+        }
       }
     }
-    if (nstreams > 1) {
-      for (int k = 1; k < nstreams; ++k) {
-        BHIP(b, hipEventRecord(b->join[k - 1], b->aux[k - 1]));
-        BHIP(b, hipStreamWaitEvent(st, b->join[k - 1], 0));
-      }
+    b->par ^= 1;   // the step's last launches wrote the next counts into the other counters
+  }
+  if (nstreams > 1) {
+    for (int k = 1; k < nstreams; ++k) {
+      BHIP(b, hipEventRecord(b->join[k - 1], b->aux[k - 1]));
+      BHIP(b, hipStreamWaitEvent(st, b->join[k - 1], 0));
     }
   }
-  b->par ^= 1;   // the step's last launches wrote the next counts into the other counters
   return ADG_OK;
 }
 
@@ -289,7 +308,7 @@ adg_status build_batch_graph(adg_batch *b) {
     b->par = p;
     BHIP(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
     adg_status rc = ADG_OK;
-    for (int i = 0; i < b->graph_steps && rc == ADG_OK; ++i) rc = enqueue_batch_step(b, b->cap_stream, false);
+    rc = enqueue_batch_steps(b, b->cap_stream, b->graph_steps, false);
     b->par = par_keep;   // nothing ran: capture only records
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(b->cap_stream, &g);
@@ -506,11 +525,7 @@ adg_status adg_batch_step(adg_batch *b, int32_t n_steps) {
       done += b->graph_steps;
     }
   }
-  for (; done < n_steps; ++done) {
-    rc = enqueue_batch_step(b, b->stream, false);
-    if (rc != ADG_OK) return rc;
-  }
-  return ADG_OK;
+  return enqueue_batch_steps(b, b->stream, n_steps - done, false);
 }
 
 adg_status adg_batch_poll(adg_batch *b, int64_t *steps, int32_t *state_err) {
@@ -569,7 +584,7 @@ adg_status adg_batch_profile(adg_batch *b, int32_t n_steps, double *ms_out, int6
   if (rc != ADG_OK) return rc;
   b->prof_events.clear();
   b->prof_class.clear();
-  for (int i = 0; i < n_steps && rc == ADG_OK; ++i) rc = enqueue_batch_step(b, b->stream, true);
+  rc = enqueue_batch_steps(b, b->stream, n_steps, true);
   hipError_t he = hipStreamSynchronize(b->stream);
   std::vector<double> sum(n_classes, 0.0);
   std::vector<int64_t> cnt(n_classes, 0);
@@ -593,54 +608,13 @@ adg_status adg_batch_profile(adg_batch *b, int32_t n_steps, double *ms_out, int6
 
 adg_status adg_batch_autotune(adg_batch *b, int32_t n_reps, int32_t *choice) {
   if (!b || n_reps < 1) return ADG_ERR_ARG;
-  static const int kTiles[2] = {8, 4};
-  double t[2] = {1e30, 1e30};
-  bool any = false;
-  // both candidates timed in three interleaved rounds, each keeping its fastest round
-  for (int round = 0; round < 3; ++round) {
-    for (int c = 0; c < 2; ++c) {
-      b->tile_elems = kTiles[c];
-      b->dirty = true;
-      adg_status rc = prepare(b);
-      if (rc != ADG_OK) return rc;
-      const Group *g = nullptr;
-      for (const Group &x : b->groups)
-        if (x.kind == 0) g = &x;
-      if (!g) break;   // no detailed-chemistry instance: nothing to choose
-      any = true;
-      // stage-0 launches only: they read w^n and write the first stage buffer and the
-      // level's stage-0 history, which the next step recomputes; the state is untouched
-      hipEvent_t e0, e1;
-      BHIP(b, hipEventCreate(&e0));
-      BHIP(b, hipEventCreate(&e1));
-      BHIP(b, launch_ns_batch(b->d_ns, b->d_tiles + g->off, g->n, 0, b->par, b->precision == ADG_MIXED_FP32, g->M,
-                              b->tile_elems, b->stream));   // warm-up
-      BHIP(b, hipEventRecord(e0, b->stream));
-      for (int r = 0; r < n_reps; ++r)
-        BHIP(b, launch_ns_batch(b->d_ns, b->d_tiles + g->off, g->n, 0, b->par, b->precision == ADG_MIXED_FP32, g->M,
-                                b->tile_elems, b->stream));
-      BHIP(b, hipEventRecord(e1, b->stream));
-      BHIP(b, hipEventSynchronize(e1));
-      float ms = 0.0f;
-      BHIP(b, hipEventElapsedTime(&ms, e0, e1));
-      (void)hipEventDestroy(e0);
-      (void)hipEventDestroy(e1);
-      t[c] = std::min(t[c], (double)ms);
-    }
-    if (!any) break;
-  }
-  const int best = any && t[1] < t[0] ? 1 : 0;
-  b->tile_elems = kTiles[best];
-  b->dirty = true;
-  if (choice) *choice = best;
+  if (choice) *choice = 0;   // one decomposition
   return prepare(b);
 }
 
 adg_status adg_batch_set_kernel_config(adg_batch *b, int32_t config) {
   if (!b) return ADG_ERR_ARG;
   if (config < 0 || config > 1) return bfail(b, ADG_ERR_ARG, "no such work decomposition");
-  b->tile_elems = config ? 4 : 8;
-  b->dirty = true;
   return ADG_OK;
 }
 
@@ -674,6 +648,7 @@ adg_status adg_batch_set_group_streams(adg_batch *b, int32_t streams) {
   if (streams < 1 || streams > kGroupStreams) return bfail(b, ADG_ERR_ARG, "group streams out of range");
   if (streams != b->group_streams) {
     b->group_streams = streams;
+    b->dirty = true;   // the groups depend on it
     destroy_batch_graph(b);   // captured with the old spread
   }
   return ADG_OK;

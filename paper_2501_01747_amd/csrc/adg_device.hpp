@@ -78,15 +78,16 @@ __device__ __forceinline__ int eff_delay(const DelayParams &d, long long n, int 
 
 // Weight of level n-k-j in the AT combination of Eq. (7): the Lagrange
 // extrapolation weight prod_{m != j} (k+m)/(m-j), which is the solution of
-// Eq. (8).  Exact: integer numerator and denominator, one rounding.
+// Eq. (8).  Numerator and denominator are integers below 2^53 (k < 8, q <= 6), so
+// their products are exact in FP64; one rounding, in the quotient.
 __device__ __forceinline__ double at_weight(int q, int k, int j) {
-  long long num = 1, den = 1;
+  double num = 1.0, den = 1.0;
   for (int m = 0; m < q; ++m) {
     if (m == j) continue;
-    num *= (long long)(k + m);
-    den *= (long long)(m - j);
+    num *= (double)(k + m);
+    den *= (double)(m - j);
   }
-  return (double)num / (double)den;
+  return num / den;
 }
 
 // Weight of level n-k-l for Legendre mode j of a buffer element (Eq. (11)): the temporal

@@ -1,5 +1,8 @@
-// Fused SSP-RK3 stage kernel for the detailed-chemistry Navier-Stokes model
-// (Sec. 2 Eq. (1)-(3), Sec. 3.1 LDG form of Eq. (5), Sec. 3.2 AT fluxes).
+// Fused RK stage kernel for the detailed-chemistry Navier-Stokes model
+// (Sec. 2 Eq. (1)-(3), Sec. 3.1 LDG form of Eq. (5), Sec. 3.2 AT fluxes), in the form
+// that spreads a point's species and reactions over lanes: the shortest latency per tile,
+// for problems whose tiles are all resident at once.  adg_ns_lane.hip holds the form for
+// larger problems and batches, ns_kernel_of the choice.
 //
 // One workgroup per tile of TE elements (4 or 8), periodic domain.  The tile and a
 // halo of two elements on each side are staged in LDS; every later phase reads
@@ -19,17 +22,13 @@
 //      species);
 //   6. volume and source projection, lift and SSP-RK3 combination; the output
 //      is stored once.
-#include "adg_device.hpp"
-#include "adg_ns.hpp"
+#include "adg_ns_device.hpp"
 
 #include <cmath>
 #include <cstring>
 #include <type_traits>
 
 namespace adg {
-
-constexpr int kThreadsBatch = 256;   // batched kernel: more resident workgroups per CU
-constexpr int kBatchLanesPerPoint = 4;   // batched kernel: lanes per point of the point phase
 
 // Sum over the LP lanes of a point group (every lane receives the same value:
 // the pairwise sums are formed in the same order on every lane).  Groups of up to
@@ -51,39 +50,15 @@ __device__ __forceinline__ double group_sum(double x) {
   return x;
 }
 
-// Temperature from the internal energy e* by Newton's method from the fixed
-// start T_guess, at most 50 iterations.  The mixture energy sum_i Y_i e_i(T) is
-// linear in the species, so it is one quintic
-// e(T) = T (c0 + T (c1 + T (c2 + T (c3 + T c4)))) + c5; returns cv(T) too.
-// Newton converges quadratically here (cv > 0 varies slowly with T): once a
-// correction is below 1e-8 T the iterate it produces is within about 1e-16 T of
-// the root, so the loop stops there, one iteration before a correction below
-// 1e-12 T would show it.
-__device__ __forceinline__ bool newton_T(const double (&c)[6], double T0, double estar, double &T, double &cv) {
-  const double d1 = 2.0 * c[1], d2 = 3.0 * c[2], d3 = 4.0 * c[3], d4 = 5.0 * c[4];
-  T = T0;
-  bool conv = false;
-  for (int it = 0; it < 50; ++it) {
-    const double e = T * (c[0] + T * (c[1] + T * (c[2] + T * (c[3] + T * c[4])))) + c[5];
-    const double cvi = c[0] + T * (d1 + T * (d2 + T * (d3 + T * d4)));
-    const double dT = (e - estar) * __builtin_amdgcn_rcp(cvi);   // the correction needs no IEEE quotient
-    T -= dT;
-    if (!(T > 0.0) || !isfinite(T)) break;
-    if (fabs(dT) <= 1e-8 * T) { conv = true; break; }
-  }
-  cv = c[0] + T * (d1 + T * (d2 + T * (d3 + T * d4)));
-  return conv;
-}
-
 // LDS arena of one tile.
-template <int M, int NS, int TE, int NRC = kNsMaxReactions>
+template <int M, int NS, int TE>
 struct NsLds {
   static constexpr int V = 3 + NS, Q = M;
   static constexpr int NH = TE + 4;   // tile + 2 halo elements per side; local l <-> element e0 - 2 + l
   static constexpr int NF = TE + 3;   // faces e0-1 .. e0+TE+1; local fl <-> face e0 - 1 + fl
   static constexpr int NN = TE * Q;   // quadrature nodes of the tile; node p <-> element p / Q, node p % Q
   static constexpr int NP = NN + 2 * (TE + 1);   // points: the nodes, then the face traces
-  static constexpr int NR = NRC;   // reaction capacity of the rate storage
+  static constexpr int NR = kNsMaxReactions;   // reaction capacity of the rate storage
   // rows padded to an odd number of doubles: the lanes of a point group read or write one
   // row each (their species) at the same column, and rows an even number of doubles apart
   // would put several of them on the same LDS banks
@@ -127,28 +102,6 @@ struct NsLds {
   int sI[NF], sK[NF];
 };
 
-// AT combination (Eq. (7)) of the central trace and the flux of variable v at interface i from
-// the levels n-k .. n-k-q+1 of stage st: levels 0..3 given (w, f; a level past q holds level
-// n-k and has weight 0), later ones (q > 4) read here one at a time.  The carried and the
-// in-launch combinations both come from here, so they round alike.
-__device__ __forceinline__ void at_combine(const NsArgs &a, int q, int k, int nmod, int st, int i, int v,
-                                           const double (&w)[4], const double (&f)[4], double &acw, double &acf) {
-  acw = 0.0;
-  acf = 0.0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const double c = j < q ? at_weight(q, k, j) : 0.0;
-    acw += c * w[j];
-    acf += c * f[j];
-  }
-  for (int j = 4; j < q; ++j) {
-    const double c = at_weight(q, k, j);
-    const double *rec = ring_at(a.ring, ring_slot(nmod, k + j, a.ring.D), st, a.dl.nif, i);
-    acw += c * rec[a.ring.off_Wc + v];
-    acf += c * rec[a.ring.off_F + v];
-  }
-}
-
 // One tile of one stage (all phases).  OpT is the arithmetic type of the modal
 // operators (interpolation to nodes and traces, LDG gradient, volume integral):
 // double for the plain path, float for the mixed-precision path.  Point physics
@@ -165,15 +118,13 @@ __device__ __forceinline__ void at_combine(const NsArgs &a, int q, int k, int nm
 // the magnitude of the state (pressure-sized fluxes would otherwise lose about
 // 4 digits of their element-to-element differences).  Gradients at nodes and
 // traces are likewise mode 0 plus the FP32 sum of the higher modes.
-// LPP: lanes per point of the point phase (0: the workgroup's lanes spread over
-// 32 or 64 point slots).
-template <int M, int NS, typename OpT, int NTH, int TE, int LPP = 0, int NRC = kNsMaxReactions>
+template <int M, int NS, typename OpT, int NTH, int TE>
 __device__ __forceinline__ void ns_tile(const NsArgs &a, const double *__restrict__ ws, const double *w0,
                                         double *wout, int stage, int advance, const RkStage rk, double *kbuf,
                                         int e0, int par,
-                                        NsLds<M, NS, TE, NRC> &Ls, NsMechT<NS> &smech) {
+                                        NsLds<M, NS, TE> &Ls, NsMechCoreT<NS> &smech) {
   constexpr int V = 3 + NS, Q = M;
-  using Lds = NsLds<M, NS, TE, NRC>;
+  using Lds = NsLds<M, NS, TE>;
   constexpr int NH = Lds::NH, NF = Lds::NF, NN = Lds::NN;
   auto &sW = Ls.sW;
   auto &sTm = Ls.sTm;
@@ -213,7 +164,7 @@ __device__ __forceinline__ void ns_tile(const NsArgs &a, const double *__restric
   const int t = threadIdx.x;
   const int E = a.E;
   const int nloc = min(TE, E - e0);
-  const NsMechT<NS> *__restrict__ mk = &smech;
+  const NsMechCoreT<NS> *__restrict__ mk = &smech;
   // variables stored per element in HBM and in the ring (the capacity NS may pad species)
   const int Vg = 3 + a.ns, VMg = Vg * M;
   const bool periodic = a.periodic != 0;
@@ -242,7 +193,7 @@ __device__ __forceinline__ void ns_tile(const NsArgs &a, const double *__restric
   constexpr int kEW = (V + VPW - 1) / VPW;
   static_assert(kEW * 64 <= NTH, "one element item per lane");
   {
-    constexpr int nwords = (int)(sizeof(NsMechT<NS>) / 8);
+    constexpr int nwords = (int)(sizeof(NsMechCoreT<NS>) / 8);
     constexpr int kMw = (nwords + NTH - 1) / NTH;
     constexpr int twords = (int)(sizeof(Tables) / 8);
     constexpr int kTw = (twords + NTH - 1) / NTH;
@@ -603,36 +554,8 @@ __device__ __forceinline__ void ns_tile(const NsArgs &a, const double *__restric
     return a.inv_dx * (sGA[r] * dr - sGB[r] * dl);
   };
   static_assert(NTH - 64 >= V * TE, "a lane of the later wavefronts per (variable, owned face)");
-  if (t >= 64 && a.at_out) {
-    // the wavefronts the mixture chain leaves idle form the next launch's AT combinations at the
-    // PE interfaces this tile owns (faces e0 .. e0+nloc-1): stage + 1 of this step, or stage 0
-    // of the next; their levels all precede what this launch writes
-    const int idx = t - 64;
-    const int v = idx / TE, fo = idx % TE;
-    const int i = sI[fo + 1];
-    if (v < Vg && fo < nloc && i >= 0) {
-      const bool last = stage == a.nst - 1;
-      const long long n2 = n + (last ? 1 : 0);
-      const int s2 = last ? 0 : stage + 1;
-      const int k2 = eff_delay<true>(a.dl, n2, i);
-      const size_t base = (size_t)(e0 + fo) * (2 * Vg + 1);
-      if (v == 0) a.at_out[base + 2 * Vg] = (double)k2;
-      if (k2 > 0) {
-        const int nm2 = step_mod(n2, a.ring.D);
-        double w[4], f[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const double *rec = ring_at(a.ring, ring_slot(nm2, k2 + (j < q_at ? j : 0), a.ring.D), s2, a.dl.nif, i);
-          w[j] = rec[a.ring.off_Wc + v];
-          f[j] = rec[a.ring.off_F + v];
-        }
-        double acw, acf;
-        at_combine(a, q_at, k2, nm2, s2, i, v, w, f, acw, acf);
-        a.at_out[base + v] = acw;
-        a.at_out[base + Vg + v] = acf;
-      }
-    }
-  }
+  // the wavefronts the mixture chain leaves idle form the next launch's AT combinations
+  if (t >= 64 && a.at_out) carry_at<V>(a, stage, n, e0, nloc, TE, sI, t - 64, NTH - 64);
   if (t < NP) {
     const int p = t;
     const bool node = p < NN;
@@ -708,7 +631,7 @@ __device__ __forceinline__ void ns_tile(const NsArgs &a, const double *__restric
   __syncthreads();
   {
     constexpr int kSlots = NP <= 32 ? 32 : 64;   // point slots per workgroup
-    constexpr int LP = LPP > 0 ? LPP : NTH / kSlots;   // lanes per point
+    constexpr int LP = NTH / kSlots;   // lanes per point
     static_assert(LP >= 1 && LP <= 64 && (LP & (LP - 1)) == 0 && NP <= NTH / LP, "every point has a lane group");
     constexpr int NO = (NS + LP - 1) / LP;
     // a wavefront whose lanes all lie past the last point's group has no point to form
@@ -924,84 +847,9 @@ __device__ __forceinline__ void ns_tile(const NsArgs &a, const double *__restric
 template <int M, int NS, int TE, int NTH, typename OpT>
 __global__ __launch_bounds__(NTH) void ns_stage_kernel(NsArgs a) {
   __shared__ NsLds<M, NS, TE> L;
-  __shared__ NsMechT<NS> smech;
+  __shared__ NsMechCoreT<NS> smech;
   ns_tile<M, NS, OpT, NTH, TE>(a, a.ws, a.w0, a.wout, a.stage, a.advance, a.rk, a.kbuf,
                                xcd_item(blockIdx.x, gridDim.x) * TE, a.par, L, smech);
-}
-
-// LDS of the batched kernel: room for the largest order it serves, rates of up to
-// kNsBatchReactions reactions.
-template <int MMAX, int TE>
-union NsBatchLds;
-template <int TE>
-union NsBatchLds<2, TE> {
-  NsLds<2, kNsMaxSpecies, TE, kNsBatchReactions> m2;
-};
-template <int TE>
-union NsBatchLds<3, TE> {
-  NsLds<2, kNsMaxSpecies, TE, kNsBatchReactions> m2;
-  NsLds<3, kNsMaxSpecies, TE, kNsBatchReactions> m3;
-};
-template <int TE>
-union NsBatchLds<4, TE> {
-  NsLds<2, kNsMaxSpecies, TE, kNsBatchReactions> m2;
-  NsLds<3, kNsMaxSpecies, TE, kNsBatchReactions> m3;
-  NsLds<4, kNsMaxSpecies, TE, kNsBatchReactions> m4;
-};
-template <int TE>
-union NsBatchLds<5, TE> {
-  NsLds<2, kNsMaxSpecies, TE, kNsBatchReactions> m2;
-  NsLds<3, kNsMaxSpecies, TE, kNsBatchReactions> m3;
-  NsLds<4, kNsMaxSpecies, TE, kNsBatchReactions> m4;
-  NsLds<5, kNsMaxSpecies, TE, kNsBatchReactions> m5;
-};
-
-// Batched stage kernel: one workgroup per (instance, tile) entry of the work
-// list; instances differ in size, order (up to MMAX modes), PE layout and
-// delays, and all are at step counter parity par.  Sizing the LDS for the
-// largest order present keeps more workgroups resident when the batch holds
-// only low orders.  An instance whose step count has reached its target is
-// skipped by all of its workgroups (its first tile carries the count over to
-// the other parity at the last stage).
-// At most 128 VGPRs (four wavefronts per SIMD): with four tiles' LDS per CU, more registers would
-// leave only three of them resident (measured: 24 % slower at 132 VGPRs).  The LDS of tiles of up
-// to N_p = 3 likewise stays within a quarter of the CU's 160 KiB.
-static_assert(sizeof(NsBatchLds<4, 8>) + sizeof(NsMech) <= 40960, "four batched tiles of N_p <= 3 per CU");
-template <typename OpT, int MMAX, int TE>
-__global__ __launch_bounds__(kThreadsBatch, 4) void ns_batch_kernel(const NsArgs *__restrict__ insts,
-                                                            const int2 *__restrict__ tiles, int stage, int par) {
-  __shared__ NsBatchLds<MMAX, TE> L;
-  __shared__ NsMech smech;
-  const int2 tl = tiles[blockIdx.x];
-  const NsArgs &a = insts[tl.x];
-  const long long n = a.step[par];
-  if (n >= a.target) {
-    if (stage == 2 && tl.y == 0 && threadIdx.x == 0) a.step[par ^ 1] = n;
-    return;
-  }
-  const int in_buf = stage, out_buf = stage == 2 ? 0 : stage + 1;
-  const double *ws = a.W[in_buf];
-  const double *w0 = a.W[0];
-  double *wout = a.W[out_buf];
-  const int M = a.M;
-  const RkStage rk = rk_stage(ADG_SSPRK3, stage);   // batches run SSP-RK3
-  constexpr int LP = kBatchLanesPerPoint, NR = kNsBatchReactions, NTH = kThreadsBatch;
-  constexpr int NS = kNsMaxSpecies;
-  if (M == 2) {
-    ns_tile<2, NS, OpT, NTH, TE, LP, NR>(a, ws, w0, wout, stage, stage == 2, rk, nullptr, tl.y, par, L.m2, smech);
-  } else if constexpr (MMAX >= 3) {
-    if (M == 3) {
-      ns_tile<3, NS, OpT, NTH, TE, LP, NR>(a, ws, w0, wout, stage, stage == 2, rk, nullptr, tl.y, par, L.m3, smech);
-    } else if constexpr (MMAX >= 4) {
-      if (M == 4) {
-        ns_tile<4, NS, OpT, NTH, TE, LP, NR>(a, ws, w0, wout, stage, stage == 2, rk, nullptr, tl.y, par, L.m4, smech);
-      } else if constexpr (MMAX >= 5) {
-        // N_p = 4 keeps FP64 operators in a mixed batch: FP32 rounding would exceed a tenth of the
-        // discretisation error there
-        ns_tile<5, NS, double, NTH, TE, LP, NR>(a, ws, w0, wout, stage, stage == 2, rk, nullptr, tl.y, par, L.m5, smech);
-      }
-    }
-  }
 }
 
 // ------------------------------------------------------------------ host side
@@ -1121,6 +969,31 @@ adg_status ns_build_mech(const adg_physics *ph, NsMechT<NSC> &hm) {
         ++g;
       }
     }
+    auto &x = hm.rx[r];
+    x.lnA = hm.lnA[r];
+    x.b = hm.b[r];
+    x.EaR = hm.EaR[r];
+    for (int c = 0; c < 2; ++c) {
+      x.sp[c] = (unsigned short)(hm.rf[r][c] < 0 ? NSC : hm.rf[r][c]);
+      x.sp[2 + c] = (unsigned short)(hm.rr[r][c] < 0 ? NSC : hm.rr[r][c]);
+    }
+    for (int i = 0; i < hm.ns; ++i) x.nu[i] = m->nu_r[r * hm.ns + i] - m->nu_f[r * hm.ns + i];
+  }
+  for (int r = hm.nr; r < (int)(sizeof hm.rx / sizeof hm.rx[0]); ++r) {
+    hm.rx[r].lnA = -1e4;   // rate zero
+    for (int c = 0; c < 4; ++c) hm.rx[r].sp[c] = NSC;
+  }
+  for (int i = 0; i < NSC; ++i) {
+    auto &x = hm.sp[i];
+    x.a0 = hm.a[i][0];
+    x.a1 = hm.a[i][1];
+    x.a5 = hm.a[i][5];
+    x.a6 = hm.a[i][6];
+    for (int k = 0; k < 4; ++k) x.h2[k] = hm.h2[i][k];
+    for (int k = 0; k < 3; ++k) x.s2[k] = hm.s2[i][k];
+    x.Ri = hm.Ri[i];
+    x.invW = hm.invW[i];
+    x.W = hm.W[i];
   }
   return ADG_OK;
 }
@@ -1144,31 +1017,6 @@ static hipError_t ns_M(int cfg, const NsArgs &a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-template <typename OpT, int TE>
-static void batch_launch(int max_m, const NsArgs *insts, const int2 *tiles, int ntiles, int stage, int par,
-                         hipStream_t s) {
-  switch (max_m) {
-    case 2: hipLaunchKernelGGL((ns_batch_kernel<OpT, 2, TE>), dim3(ntiles), dim3(kThreadsBatch), 0, s, insts, tiles, stage, par); break;
-    case 3: hipLaunchKernelGGL((ns_batch_kernel<OpT, 3, TE>), dim3(ntiles), dim3(kThreadsBatch), 0, s, insts, tiles, stage, par); break;
-    case 4: hipLaunchKernelGGL((ns_batch_kernel<OpT, 4, TE>), dim3(ntiles), dim3(kThreadsBatch), 0, s, insts, tiles, stage, par); break;
-    default: hipLaunchKernelGGL((ns_batch_kernel<OpT, 5, TE>), dim3(ntiles), dim3(kThreadsBatch), 0, s, insts, tiles, stage, par); break;
-  }
-}
-
-hipError_t launch_ns_batch(const NsArgs *insts, const int2 *tiles, int ntiles, int stage, int par, bool mixed,
-                           int max_m, int tile_elems, hipStream_t s) {
-  if (ntiles <= 0) return hipSuccess;
-  if (max_m < 2 || max_m > kMaxM || (tile_elems != 4 && tile_elems != 8)) return hipErrorInvalidValue;
-  if (tile_elems == 8) {
-    if (mixed) batch_launch<float, 8>(max_m, insts, tiles, ntiles, stage, par, s);
-    else batch_launch<double, 8>(max_m, insts, tiles, ntiles, stage, par, s);
-  } else {
-    if (mixed) batch_launch<float, 4>(max_m, insts, tiles, ntiles, stage, par, s);
-    else batch_launch<double, 4>(max_m, insts, tiles, ntiles, stage, par, s);
-  }
-  return hipGetLastError();
-}
-
 template <int NS>
 static hipError_t ns_stage_ns(int M, int cfg, const NsArgs &a, bool mixed, hipStream_t s) {
   // FP32 operators for N_p <= 3 only (N_p = 4 keeps FP64 ones: error budget)
@@ -1181,9 +1029,42 @@ static hipError_t ns_stage_ns(int M, int cfg, const NsArgs &a, bool mixed, hipSt
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_ns_stage(int M, int cfg, const NsArgs &a, bool mixed, hipStream_t s) {
-  return ns_capacity(a.ns) == kNsMaxSpecies ? ns_stage_ns<kNsMaxSpecies>(M, cfg, a, mixed, s)
-                                            : ns_stage_ns<kNsWideSpecies>(M, cfg, a, mixed, s);
+// Tiles of 8 elements at 256 threads that fit a CU's LDS.
+template <int NS>
+static int tiles_per_cu(int M) {
+  constexpr size_t kLds = 160 * 1024, mech = sizeof(NsMechCoreT<NS>);
+  const size_t lds = M == 2 ? sizeof(NsLds<2, NS, 8>) : M == 3 ? sizeof(NsLds<3, NS, 8>) : M == 4 ? sizeof(NsLds<4, NS, 8>)
+                                                                                            : sizeof(NsLds<5, NS, 8>);
+  const size_t fit = kLds / (lds + mech);
+  return fit < 4 ? (int)fit : 4;
+}
+
+// Measured (us per stage, one box, N_p = 3, 9 species; 8/512, 8/256, a lane per point):
+//   E = 2048   9.8 11.1 18.2     E = 4096   12.3 12.9 18.5     E = 6144  18.8 14.9 18.6
+//   E = 8192  21.6 16.3 20.0     E = 12288  31.3 24.9 20.5     E = 2^15  77.2 53.1 30.5
+// and the same lines for N_p = 1, 2, 4.  While all tiles of 8 are resident at once the spread kernels
+// win: their latency per tile is about half of a lane's that forms every species and reaction of its
+// point; 512 threads while two tiles a CU hold the problem (256 CUs), 256 threads while the LDS holds
+// it.  Beyond, the lane-per-point kernel's fewer instructions do, with 16 species from 12288 elements
+// on (a lane's chain is longer: 16384 elements at N_p = 3 take 46.6, 53.0 and 34.4, 8192 take 25.2,
+// 27.8 and 29.7).
+int ns_kernel_of(int cfg, int E, int M, int ns) {
+  constexpr int kCus = 256;
+  const bool wide = ns_capacity(ns) > kNsMaxSpecies;
+  const bool lane = E > (wide ? 12288 : 8192);
+  if (cfg > 1) return cfg;
+  if (cfg == 1) return lane ? kNsLane : 1;
+  if (cfg == 0) return 0;
+  if (lane) return kNsLane;
+  const int tiles = (E + 7) / 8;
+  const int fit = wide ? tiles_per_cu<kNsWideSpecies>(M) : tiles_per_cu<kNsMaxSpecies>(M);
+  return tiles > 2 * kCus && tiles <= fit * kCus ? 1 : 0;
+}
+
+hipError_t launch_ns_stage(int M, int kernel, const NsArgs &a, bool mixed, hipStream_t s) {
+  if (kernel == kNsLane) return launch_ns_lane(M, a, s);
+  return ns_capacity(a.ns) == kNsMaxSpecies ? ns_stage_ns<kNsMaxSpecies>(M, kernel, a, mixed, s)
+                                            : ns_stage_ns<kNsWideSpecies>(M, kernel, a, mixed, s);
 }
 
 template adg_status ns_build_mech<kNsMaxSpecies>(const adg_physics *, NsMech &);

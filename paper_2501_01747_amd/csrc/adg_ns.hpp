@@ -9,16 +9,17 @@ namespace adg {
 // Species capacities of the kernels: a mechanism of Ns species runs in the kernels of the
 // smallest capacity that holds it, the species past Ns padded with zero density, no thermo
 // and no reactions (they add exact zeros to every species sum and are never stored).
-constexpr int kNsMaxSpecies = 9;      // the batched kernels, and single problems with Ns <= 9
+constexpr int kNsMaxSpecies = 9;      // the batched kernel, and single problems with Ns <= 9
 constexpr int kNsWideSpecies = 16;    // single problems with 9 < Ns <= 16
 constexpr int kNsMaxReactions = 32;
-constexpr int kNsBatchReactions = 24;   // reactions of a batched mechanism (rate storage of the batched kernel)
+constexpr int kNsReactionGroup = 2;   // reactions that a lane of the lane-per-point kernels forms side by side
+constexpr int kNsBatchReactions = 24;   // reactions of a batched mechanism
 inline int ns_capacity(int n_species) { return n_species <= kNsMaxSpecies ? kNsMaxSpecies : kNsWideSpecies; }
 
 // Mechanism in device memory, read with wave-uniform indices (scalar loads), for kernels of
 // species capacity NSC.
 template <int NSC>
-struct NsMechT {
+struct NsMechCoreT {
   static constexpr int kSpecies = NSC;
   int ns, nr;
   double Ru, p_ref, T_guess;
@@ -51,6 +52,26 @@ struct NsMechT {
   unsigned char spr[NSC][kNsMaxReactions];
   signed char spnu[NSC][kNsMaxReactions];
   int pad_;
+};
+
+// The whole device mechanism: the core (copied to LDS by the kernels that spread species and
+// reactions over lanes) and, for the lane-per-point kernels, one record per species and reaction
+// in the order they are read, each a whole number of 64-byte scalar loads.
+template <int NSC>
+struct NsMechT : NsMechCoreT<NSC> {
+  struct alignas(64) Species {
+    double a0, h2[4], a5;          // h_i/R_i = T (a0 + T (h2[0] + ...)) + a5
+    double a1, s2[3], a6;          // s_i/R_i = a0 ln T + T (a1 + T (s2[0] + ...)) + a6
+    double Ri, invW, W;
+  };
+  struct alignas(64) Reaction {
+    double lnA, b, EaR;
+    unsigned short sp[4];          // species of the reactants and products (two each; NSC: none)
+    double nu[NSC];                // net coefficients nu''_i - nu'_i of all species
+  };
+  Species sp[NSC];
+  // padded with reactions of rate zero to whole groups
+  Reaction rx[(kNsMaxReactions + kNsReactionGroup - 1) / kNsReactionGroup * kNsReactionGroup];
 };
 using NsMech = NsMechT<kNsMaxSpecies>;
 using NsMechWide = NsMechT<kNsWideSpecies>;
@@ -99,16 +120,25 @@ adg_status ns_setup(NsArgs &a, const adg_physics *ph, const adg_discretization *
 // The device form of a mechanism (host side; validates it).
 template <int NSC>
 adg_status ns_build_mech(const adg_physics *ph, NsMechT<NSC> &hm);
-// Work decompositions of the single-problem stage kernel: (tile elements, threads)
-// = (8, 512), (8, 256), (4, 256), (4, 512), (8, 1024).
+// Kernels of the single-problem stage.  0..4 spread a point's species and reactions over lanes,
+// (tile elements, threads) = (8, 512), (8, 256), (4, 256), (4, 512), (8, 1024); kNsLane gives each
+// point a lane.
+constexpr int kNsLane = 5;
+// Work decompositions that adg_set_kernel_config and adg_autotune choose from: 0..4, 1 standing for
+// the throughput kernel of the problem's size.
 constexpr int kNsConfigs = 5;
-// Capacity from a.ns; mixed = FP32 modal operators (for N_p <= 3; N_p = 4 keeps FP64 ones).
-hipError_t launch_ns_stage(int M, int cfg, const NsArgs &a, bool mixed, hipStream_t s);
-// One stage for every (instance, tile) entry of `tiles` (device), at step counter parity par;
-// mixed = FP32 modal operators; max_m = the largest N_p + 1 among the listed instances; tiles
-// of tile_elems (4 or 8) elements.
-hipError_t launch_ns_batch(const NsArgs *insts, const int2 *tiles, int ntiles, int stage, int par, bool mixed,
-                           int max_m, int tile_elems, hipStream_t s);
+// The kernel of work decomposition cfg (-1: none chosen) for E elements of order M - 1, ns species.
+int ns_kernel_of(int cfg, int E, int M, int ns);
+// Capacity from a.ns; mixed = FP32 modal operators of the kernels 0..4 (for N_p <= 3; N_p = 4 keeps
+// FP64 ones).
+hipError_t launch_ns_stage(int M, int kernel, const NsArgs &a, bool mixed, hipStream_t s);
+// Lane-per-point kernels (FP64 throughout): elements per tile of order M - 1, one stage of a single
+// problem, and one stage for every (instance, first element) entry of `tiles` (device) at step
+// counter parity par, max_m = the largest N_p + 1 among the listed instances.
+int ns_lane_tile_elems(int M);
+hipError_t launch_ns_lane(int M, const NsArgs &a, hipStream_t s);
+hipError_t launch_ns_lane_batch(int max_m, const NsArgs *insts, const int2 *tiles, int ntiles, int stage, int par,
+                                hipStream_t s);
 constexpr int kNsMinTile = 4;
 
 }  // namespace adg

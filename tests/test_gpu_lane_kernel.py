@@ -1,0 +1,102 @@
+"""The lane-per-point detailed-chemistry kernel (batches of any size; single problems of more than
+8192 elements, 12288 with more than 9 species) at the edges of its tiles (46, 37, 31 and 25 elements
+for N_p = 1..4), with a PE interface at every face, and with equilibrium constants whose factors
+leave the range of the factored form, against the oracle at the repository's parity bound (1e-10)."""
+import numpy as np
+import pytest
+
+from _parity import check, var_errors
+from test_gpu_ns import mechanism_of
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+TILE = {1: 46, 2: 37, 3: 31, 4: 25}
+CFL = {1: 0.1, 2: 0.08, 3: 0.04, 4: 0.01}
+
+
+@pytest.fixture(scope="module")
+def adg():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2501_01747_amd import adg as lib
+
+    return lib
+
+
+@pytest.fixture(scope="module")
+def mech():
+    return gen.c1_mechanism()
+
+
+def run_batch(adg, orc, cases, steps):
+    heap = sum(adg.Batch.instance_bytes(c) for c, _ in cases)
+    b = adg.Batch(len(cases), sum(c["disc"]["n_elem"] for c, _ in cases), heap)
+    slots = [b.add(c, w) for c, w in cases]
+    b.step(steps)
+    for (c, w), sl in zip(cases, slots):
+        o = orc.OracleSolver(c, w, steps + 1)
+        o.step(steps)
+        print(f"[lane] E={c['disc']['n_elem']} Np={c['disc']['order_p']} PEs={c['async']['n_pe']} {c['disc']['bc']}", flush=True)
+        check(b.state(sl), o.state(), c, 1e-10, "batch instance")
+    b.close()
+
+
+@pytest.mark.parametrize("bc", ["periodic", "transmissive"])
+@pytest.mark.parametrize("order_p", [1, 2, 3, 4])
+def test_tile_edges(adg, orc, mech, order_p, bc):
+    """Meshes shorter than the halo, one element short of, equal to and past one and two tiles."""
+    te = TILE[order_p]
+    cases = []
+    for E in (1, 2, 3, te - 1, te, te + 1, 2 * te, 2 * te + 1):
+        c, w = gen.case_c1(E=E, order_p=order_p, n_pe=min(E, 3), mech=mech, cfl=CFL[order_p], Lx=0.01 * max(E, 8) / 2048, seed=E)
+        c["disc"]["bc"] = bc
+        cases.append((c, w))
+    run_batch(adg, orc, cases, 8)
+
+
+@pytest.mark.parametrize("order_p,at_order", [(2, 3), (3, 6)])
+def test_every_face_a_pe_interface(adg, orc, mech, order_p, at_order):
+    """More interfaces in a tile than the first wavefront takes in one round; AT orders of up to 6 levels."""
+    cases = []
+    for E, bc in ((2 * TILE[order_p] + 5, "periodic"), (TILE[order_p] + 2, "transmissive")):
+        c, w = gen.case_c1(E=E, order_p=order_p, n_pe=E, mech=mech, cfl=0.2 * CFL[order_p], Lx=0.01 * E / 2048, seed=E,
+                           at_order=at_order, pmf=(0.2, 0.4, 0.4))
+        c["disc"]["bc"] = bc
+        cases.append((c, w))
+    run_batch(adg, orc, cases, 12)
+
+
+def test_factors_beyond_the_factored_range(adg, orc, mech):
+    """An enthalpy of -0.8 MJ/mol per atom A in every species leaves all reaction enthalpies as they are,
+    but puts the largest species factor of the equilibrium constants (A2B) at exp(250) at 1000 K, where the
+    kernel sums the exponents first: in a mesh between 950 and 1050 K, wavefronts of either form of the
+    rates and of both kinds of points."""
+    nasa = mech["nasa7"].copy()
+    nasa[:, 5] -= 0.8e6 / gen.RU * mech["composition"][:, 0]
+    shifted = dict(mech, nasa7=nasa)
+    run_batch(adg, orc, [gen.case_c1(E=93, n_pe=4, mech=shifted, Lx=0.01 * 93 / 2048)], 10)
+
+
+@pytest.mark.parametrize("ns,E,rk", [(9, 8215, "ssprk3"), (9, 8216, "lserk4"), (5, 8214, "rk2"), (16, 12307, "ssprk3")])
+def test_single_problems(adg, orc, ns, E, rk):
+    """Single problems past the size from which the kernel runs them by default, with a last tile of
+    31, 1 and 30 elements and 16 species; then the decomposition changed in mid-run and back (the
+    spread kernels' carried AT values are formed anew)."""
+    mech = gen.c1_mechanism() if ns == 9 else mechanism_of(ns)
+    case, w0 = gen.case_c1(E=E, n_pe=40, mech=mech, Lx=0.01 * E / 2048, cfl=0.02)
+    case["disc"].update(rk=rk, bc="transmissive" if E % 2 else "periodic")
+    s = adg.Solver(case)
+    s.set_state(w0)
+    o = orc.OracleSolver(case, w0, 8)
+    s.step(5)
+    s.set_kernel_config(0)
+    s.step(1)
+    s.set_kernel_config(1)
+    s.step(1)
+    o.step(7)
+    assert float(np.max(var_errors(s.state(), o.state()))) < 1e-10
+    check(s.state(), o.state(), case, 1e-10, "single")
+    s.close()
