@@ -5,7 +5,7 @@
 A "step" is one full SSP-RK3 time step (DG right-hand side, chemistry, AT fluxes at
 PE interfaces, RK update, history publish; for the limited workload also the
 KXRCF/AT-WENO limiter of every stage's output): three fused stage launches, or one
-launch of all stages for the one-step model without the limiter.  The
+launch of all stages for the one-step model.  The
 metric counts scalar DOF updates (E (N_p+1) (3+N_s) per stage) per second, with
 the inputs resident in HBM before the timed region starts.
 
@@ -85,11 +85,9 @@ def pmc_probe(args):
 
 
 def launches_per_step(case) -> int:
-    """Kernel launches of one time step: one for the one-step model without the limiter (all
-    stages in one kernel), else one per RK stage."""
-    if case["physics"]["model"] == "onestep" and not case["disc"].get("limiter"):
-        return 1
-    return RK_STAGES[case["disc"].get("rk", "ssprk3")]
+    """Kernel launches of one time step: one for the one-step model (all stages in one kernel),
+    one per RK stage for the detailed-chemistry model."""
+    return 1 if case["physics"]["model"] == "onestep" else RK_STAGES[case["disc"].get("rk", "ssprk3")]
 
 
 def euler_stage_bytes(case) -> float:
@@ -103,12 +101,22 @@ def euler_stage_bytes(case) -> float:
     return gen.dof(case) * 8.0 * (2 + 3 + 3) / 3.0 + flags
 
 
-def euler_launch_bytes(case) -> float:
-    """Algorithmic HBM bytes of one launch of the one-step model: a stage's, or, where a launch
-    is a whole step, w^n read once and w^(n+1) written once (16 B/DOF)."""
+def euler_stage_bytes(case) -> float:
+    """Algorithmic HBM bytes of a stage where each is a launch of its own, averaged over the three
+    stages: stage 1 reads w^n and writes w^(1) (16 B/DOF); stages 2 and 3 read w^n and w^(s) and
+    write w^(s+1) (24 B/DOF); with the limiter one troubled-cell flag byte per element."""
     from workloads import gen
 
-    return gen.dof(case) * 16.0 if launches_per_step(case) == 1 else euler_stage_bytes(case)
+    flags = case["disc"]["n_elem"] if case["disc"].get("limiter") else 0
+    return gen.dof(case) * 8.0 * (2 + 3 + 3) / 3.0 + flags
+
+
+def euler_launch_bytes(case) -> float:
+    """Algorithmic HBM bytes of one launch of the one-step model, a whole step: w^n read once and
+    w^(n+1) written once (16 B/DOF), with the limiter one flag byte per element."""
+    from workloads import gen
+
+    return gen.dof(case) * 16.0 + (case["disc"]["n_elem"] if case["disc"].get("limiter") else 0)
 
 
 def detailed_stage_flops(case) -> float:
@@ -378,13 +386,13 @@ def region_launch_ms(s, steps: int, per_step: int, graph: int = 10) -> float:
 
 
 def hbm_points(steps: int = 20):
-    """The one-step stage kernels at sizes where HBM bounds them (the C0 physics at E = 2^22 without
+    """The one-step step kernels at large sizes (the C0 physics at E = 2^22 without
     the limiter, the C2 physics at E = 2^21 with it), each with its roofline against 8 TB/s: mean
     launch time from HIP events over graph-replayed steps on the solver's stream."""
     out = {}
     for key, res, kernel, tkey in (("c0_physics_E4194304", sweep_euler([2**22], steps)[0], "euler_step_kernel",
                                     "c0_4194304"),
-                                   ("c2_physics_E2097152", sweep_limiter([2**21], steps)[0], "euler_lim_kernel",
+                                   ("c2_physics_E2097152", sweep_limiter([2**21], steps)[0], "euler_lim_step_kernel",
                                     "c2_2097152")):
         out[key] = {"n_elem": res["n_elem"], "dof": res["dof"], "launch_ms": res["stage_ms"],
                     "roofline": {"bound": "hbm", "kernel": kernel, "achieved": res["GBps"], "peak": HBM_PEAK_GBS,
@@ -481,7 +489,7 @@ def sweep_ns(sizes, steps=20):
 
 
 def sweep_limiter(sizes, steps=20):
-    """Size sweep of the one-step stage kernel with the limiter inside (the detonation
+    """Size sweep of the one-step step kernel with the limiter inside (the detonation
     workload's physics at its resolution dx = 1/32, N_p = 3, HLLC, KXRCF + AT-WENO, 64 PEs):
     per size, the kernel's mean launch time (as in sweep_euler) and its algorithmic bandwidth."""
     import torch
@@ -583,7 +591,7 @@ def main():
     if args.sweep_euler:
         print(json.dumps({"sweep": "euler_step_kernel", "results": sweep_euler([2**p for p in range(10, 24, 1)])}),
               flush=True)
-        print(json.dumps({"sweep": "euler_lim_kernel", "results": sweep_limiter([2**p for p in range(13, 23, 1)])}),
+        print(json.dumps({"sweep": "euler_lim_step_kernel", "results": sweep_limiter([2**p for p in range(13, 23, 1)])}),
               flush=True)
         return
     case, w0 = workload(args.workload, args.n_elem)
@@ -631,7 +639,7 @@ def main():
         achieved = nbytes / (stage_ms * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": read_traffic(traffic_key, kernel_src),
-                "kernel": "euler_lim_kernel" if case["disc"].get("limiter") else "euler_step_kernel",
+                "kernel": "euler_lim_step_kernel" if case["disc"].get("limiter") else "euler_step_kernel",
                 "launch_ms": stage_ms, "bytes_per_launch": nbytes}
     d = case["disc"]
     out = {

@@ -206,7 +206,7 @@ int32_t adg_n_interfaces(const adg_solver *s);
    of kernel class i and launches_out[i] the launch count; n_classes is the
    array length (class 0: the step's kernel, which includes the limiter of a
    limited problem; there is one launch per RK stage, or one per step for the
-   one-step model without the limiter).
+   one-step model).
    Synchronises. */
 adg_status adg_profile(adg_solver *s, int32_t n_steps, double *ms_out, int64_t *launches_out, int32_t n_classes);
 

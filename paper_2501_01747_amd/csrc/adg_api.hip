@@ -105,17 +105,15 @@ void set_at_buffers(const adg_solver *s, NsArgs &a, int stage) {
 
 // The state buffer and step counter parity after one time step from (cur, par).
 void next_alignment(const adg_solver *s, int &cur, int &par) {
-  const int S = s->P.lay.S;
-  if (s->P.phys.model == ADG_ONESTEP && !s->P.disc.limiter) cur = 1 - cur;
-  else if (rk_stage(s->P.disc.rk, 0).two_n) cur = (cur + S) % 2;
-  else if (s->P.phys.model == ADG_ONESTEP) cur = 1 - cur;
+  if (s->P.phys.model == ADG_ONESTEP) cur = 1 - cur;
+  else if (rk_stage(s->P.disc.rk, 0).two_n) cur = (cur + s->P.lay.S) % 2;
   par ^= 1;   // the step's last launch wrote the next count into the other counter
 }
 
 adg_status enqueue_step(adg_solver *s, hipStream_t st, TimerFn timer) {
   const int M = s->P.lay.M, S = s->P.lay.S;
   const int rk = s->P.disc.rk;
-  if (s->P.phys.model == ADG_ONESTEP && !s->P.disc.limiter) {
+  if (s->P.phys.model == ADG_ONESTEP) {
     // the whole step in one launch; its halo lanes read other wavefronts' elements, so the
     // state alternates between buffers 0 and 1
     EulerArgs a = s->P.ea;
@@ -123,7 +121,7 @@ adg_status enqueue_step(adg_solver *s, hipStream_t st, TimerFn timer) {
     a.wout = s->P.W[1 - s->cur];
     a.par = s->par;
     if (timer) timer(s, 0, true);
-    HIP_TRY(s, launch_euler_step(M, s->P.disc.flux, S, a, st));
+    HIP_TRY(s, launch_euler_step(M, s->P.disc.flux, S, a, s->P.disc.limiter ? &s->P.la : nullptr, st));
     if (timer) timer(s, 0, false);
     next_alignment(s, s->cur, s->par);
     return ADG_OK;
@@ -131,52 +129,25 @@ adg_status enqueue_step(adg_solver *s, hipStream_t st, TimerFn timer) {
   const int in_buf[3] = {0, 1, 2}, out_buf[3] = {1, 2, 0};
   for (int stage = 0; stage < S; ++stage) {
     const RkStage r = rk_stage(rk, stage);
-    // Shu-Osher SSP-RK3: w^n in buffer 0, stages in 1 and 2, the last stage back into 0;
-    // with the limiter no stage may write a buffer it reads, so w^n alternates between
-    // buffers 0 and 1 (s->cur), stage 1 goes to the other one, stage 2 to buffer 2 and
-    // stage 3 to the other one again.  2N schemes: the state alternates between buffers
-    // 0 and 1 (s->cur holds it at the start of the step), the register is buffer 2
-    // (with the limiter, buffers 2 and 3 alternate the same way).
-    const bool limited = s->P.phys.model == ADG_ONESTEP;
-    const bool alt = !r.two_n && limited;
-    const int lim_in[3] = {s->cur, 1 - s->cur, 2}, lim_out[3] = {1 - s->cur, 2, 1 - s->cur};
-    const int bi = r.two_n ? (s->cur + stage) % 2 : alt ? lim_in[stage] : in_buf[stage];
-    const int bo = r.two_n ? (s->cur + stage + 1) % 2 : alt ? lim_out[stage] : out_buf[stage];
-    const bool last = stage == S - 1;
-    if (limited) {
-      EulerArgs a = s->P.ea;
-      a.alt = 0;   // buffers chosen here (the batched kernels choose them by step parity)
-      a.w0 = s->P.W[alt ? s->cur : 0];
-      a.ws = s->P.W[bi];
-      a.wout = s->P.W[bo];
-      if (r.two_n) {
-        // the two registers alternate like the state: read W[2 + bi], write W[2 + bo]
-        a.kbuf = s->P.W[2 + bi];
-        a.kout = s->P.W[2 + bo];
-      }
-      a.stage = stage;
-      a.rk = r;
-      a.advance = last;
-      a.par = s->par;
-      if (timer) timer(s, 0, true);
-      HIP_TRY(s, launch_euler_lim(M, s->P.disc.flux, a, s->P.la, st));
-      if (timer) timer(s, 0, false);
-    } else {
-      NsArgs a = s->P.na;
-      a.w0 = s->P.W[0];
-      a.ws = s->P.W[bi];
-      a.wout = s->P.W[bo];
-      a.stage = stage;
-      a.rk = r;
-      a.advance = last;
-      a.par = s->par;
-      set_at_buffers(s, a, stage);
-      if (timer) timer(s, 0, true);
-      const int kernel = ns_kernel(s, s->ns_cfg);
-      HIP_TRY(s, launch_ns_stage(M, kernel, a, s->P.disc.precision == ADG_MIXED_FP32, st));
-      s->at_ready = kernel != kNsLane;
-      if (timer) timer(s, 0, false);
-    }
+    // Shu-Osher SSP-RK3: w^n in buffer 0, stages in 1 and 2, the last stage back into 0.
+    // 2N schemes: the state alternates between buffers 0 and 1 (s->cur holds it at the start
+    // of the step), the register is buffer 2.
+    const int bi = r.two_n ? (s->cur + stage) % 2 : in_buf[stage];
+    const int bo = r.two_n ? (s->cur + stage + 1) % 2 : out_buf[stage];
+    NsArgs a = s->P.na;
+    a.w0 = s->P.W[0];
+    a.ws = s->P.W[bi];
+    a.wout = s->P.W[bo];
+    a.stage = stage;
+    a.rk = r;
+    a.advance = stage == S - 1;
+    a.par = s->par;
+    set_at_buffers(s, a, stage);
+    if (timer) timer(s, 0, true);
+    const int kernel = ns_kernel(s, s->ns_cfg);
+    HIP_TRY(s, launch_ns_stage(M, kernel, a, s->P.disc.precision == ADG_MIXED_FP32, st));
+    s->at_ready = kernel != kNsLane;
+    if (timer) timer(s, 0, false);
   }
   next_alignment(s, s->cur, s->par);
   return ADG_OK;

@@ -6,12 +6,11 @@
 // (first fit, coalescing on release).  An admission that does not fit is
 // refused with ADG_ERR_NOMEM: admission is by device-memory footprint.
 //
-// A time step launches, per stage, one batched kernel for all detailed-
-// chemistry instances (orders dispatched inside the kernel) and one batched kernel per (order, flux) group of limited one-step instances, the limiter
-// inside that kernel; unlimited one-step instances take one launch per (order,
-// flux) group and step.  Every workgroup works on one instance
-// only, with that instance's own arguments, so the arithmetic of an instance
-// does not depend on what else is in the batch.
+// A time step launches, per stage, one batched kernel for all detailed-chemistry
+// instances (orders dispatched inside the kernel; two with many tiles), and per
+// step one batched kernel per (order, flux, limiter) group of one-step instances.
+// Every workgroup works on one instance only, with that instance's own arguments,
+// so the arithmetic of an instance does not depend on what else is in the batch.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -181,7 +180,7 @@ void rebuild_tiles(adg_batch *b) {
     Group g{kind, M, flux, lim, (int)b->h_tiles.size(), 0};
     for (int i : slots) {
       const int E = b->slots[i].P.lay.E;
-      const int nb = kind == 0 ? (E + stride(i) - 1) / stride(i) : euler_blocks(E, lim ? kEulerLimOwned : kEulerStepOwned);
+      const int nb = kind == 0 ? (E + stride(i) - 1) / stride(i) : euler_blocks(E, 3, lim);
       for (int k = 0; k < nb; ++k) b->h_tiles.push_back(make_int2(i, k * stride(i)));
     }
     g.n = (int)b->h_tiles.size() - g.off;
@@ -246,7 +245,7 @@ adg_status enqueue_batch_steps(adg_batch *b, hipStream_t st, int steps, bool tim
     for (int stage = 0; stage < 3; ++stage) {
       for (int gi = 0; gi < (int)b->groups.size(); ++gi) {
         const Group &g = b->groups[gi];
-        if (g.kind == 1 && !g.lim && stage > 0) continue;   // its whole step ran in the first launch
+        if (g.kind == 1 && stage > 0) continue;   // its whole step ran in the first launch
         const hipStream_t gs = nstreams > 1 && gi % nstreams ? b->aux[gi % nstreams - 1] : st;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (timed) {
@@ -256,7 +255,7 @@ adg_status enqueue_batch_steps(adg_batch *b, hipStream_t st, int steps, bool tim
         if (g.kind == 0) {
           BHIP(b, launch_ns_lane_batch(g.M, b->d_ns, b->d_tiles + g.off, g.n, stage, b->par, gs));
         } else {
-          BHIP(b, launch_euler_batch(g.M, g.flux, g.lim, b->d_eu, b->d_tiles + g.off, g.n, stage, b->par, gs));
+          BHIP(b, launch_euler_batch(g.M, g.flux, g.lim, b->d_eu, b->d_tiles + g.off, g.n, b->par, gs));
         }
         if (timed) {
           BHIP(b, hipEventCreate(&e1));
@@ -459,20 +458,10 @@ adg_status adg_batch_add(adg_batch *b, const adg_physics *phys, const adg_discre
   } else {
     EulerSet es;
     std::memset(&es, 0, sizeof es);
-    const int in_buf[3] = {0, 1, 2}, out_buf[3] = {1, 2, 0};
-    for (int st = 0; st < 3; ++st) {
-      EulerArgs a = P.ea;   // a.alt is set: the kernel picks the buffers
-      a.w0 = P.W[0];
-      a.ws = P.W[in_buf[st]];
-      a.wout = P.W[out_buf[st]];
-      a.stage = st;
-      a.rk = rk_stage(ADG_SSPRK3, st);
-      a.advance = st == 2;
-      a.step = P.step;
-      a.err = P.err;
-      a.target = s.target;
-      es.st[st] = a;
-    }
+    es.st = P.ea;
+    es.st.step = P.step;
+    es.st.err = P.err;
+    es.st.target = s.target;
     if (P.disc.limiter) es.lim = P.la;
     he = hipMemcpy(b->d_eu + slot, &es, sizeof es, hipMemcpyHostToDevice);
     if (he != hipSuccess) return fail_release(he, "descriptor upload");
@@ -551,7 +540,7 @@ adg_status adg_batch_get_state(adg_batch *b, int32_t slot, double *w, int64_t co
   if (count != (int64_t)L.E * VM) return bfail(b, ADG_ERR_ARG, "state size mismatch");
   // one-step instances: the state lives in buffer (step count) mod 2
   const double *src = P.W[0];
-  if (P.ea.alt) {
+  if (P.phys.model == ADG_ONESTEP) {
     long long n = 0;
     BHIP(b, hipStreamSynchronize(b->stream));
     BHIP(b, hipMemcpy(&n, P.step + b->par, sizeof n, hipMemcpyDeviceToHost));

@@ -11,7 +11,6 @@ constexpr int kMaxM = 5;      // N_p <= 4
 constexpr int kMaxQ = 5;      // Gauss points = N_p + 1
 constexpr int kMaxL = 8;      // admissible delays
 constexpr int kMaxAT = 6;     // AT order q
-constexpr int kEulerBlock = 256;
 
 // Delay model of Sec. 4 (CAA / SAA) and the start-up clamp k <= n - q + 1.
 struct DelayParams {
@@ -113,38 +112,32 @@ __host__ __device__ inline RkStage rk_stage(int rk, int s) {
   return r;
 }
 
+// The operator tables of the one-step kernel (kernel arguments: kept small).
+struct EulerTables {
+  double B[kMaxQ][kMaxM], WG[kMaxQ][kMaxM], WB[kMaxQ][kMaxM];   // as in Tables
+};
+
 struct EulerArgs {
-  const double *w0;     // w^n (may alias wout at the last stage)
-  const double *ws;     // stage input w^(s)
-  double *wout;         // stage output (unlimited)
+  const double *ws;     // w^n (the batched kernels read W[n mod 2] and write the other one)
+  double *wout;         // w^(n+1): another buffer, since halo lanes read other wavefronts' elements
   const int *face_if;   // [E+1] interface index of face f, or -1
   // step counters of the two parities: a launch of parity par works on step
-  // step[par], and the step's last launch writes step[par ^ 1] = step[par] + 1
-  // (plain stores by one workgroup: no launch of the step reads that counter)
+  // step[par] and writes step[par ^ 1] = step[par] + 1 (plain store by one workgroup:
+  // no launch of the step reads that counter)
   long long *step;
   int par;              // parity of a single-problem launch (batched launches take theirs from the launch)
-  int advance;          // this launch ends the time step
   int *err;
   long long target;     // batched launches skip the instance once its step reaches it
   int E;
   int periodic;
-  int stage;
-  RkStage rk;
-  double *kbuf;         // 2N register read by this stage (2N schemes)
-  double *kout;         // 2N register written by this stage (kbuf itself without the limiter)
-  // batched Shu-Osher steps: w^n lives in W[n mod 2] (n = the step counter) and the step
-  // ends in W[1 - n mod 2]; with the limiter stage 1 writes W[1 - n mod 2], stage 2 W[2],
-  // stage 3 W[1 - n mod 2].  No launch writes a buffer it reads (the kernels then ignore w0,
-  // ws and wout; the single-problem solver passes the same buffers explicitly)
-  int alt;
-  double *W[3];
+  double *W[2];
   int store_U;          // publish boundary-element outputs for the limiter
   double dt;
   double two_over_dx;
   OneStep ph;
   DelayParams dl;
   RingParams ring;
-  Tables tb;
+  EulerTables tb;
 };
 
 // Constants of the troubled-cell indicator and the characteristic WENO limiter
@@ -176,32 +169,22 @@ __host__ __device__ inline int xcd_item(int b, int n) {
 
 enum ErrBits { kErrState = 1, kErrNewton = 2 };
 
-// Argument blocks of one instance of the one-step model in a batch: one per stage,
-// and the limiter constants.
+// Arguments of one instance of the one-step model in a batch.
 struct EulerSet {
-  EulerArgs st[3];
+  EulerArgs st;
   LimiterArgs lim;
 };
 
 // Kernel launchers (defined in the .hip files).
-// One whole time step (`stages` = 3, 2 or 5 RK stages) of the one-step model without the
-// limiter: reads a.ws, writes a.wout (another buffer).
-hipError_t launch_euler_step(int M, int flux, int stages, const EulerArgs &a, hipStream_t s);
-// One stage of the one-step model with the limiter in the same kernel.
-hipError_t launch_euler_lim(int M, int flux, const EulerArgs &a, const LimiterArgs &lim, hipStream_t s);
-// Batched one-step launch over a work list of (instance, block) entries, all of order M,
-// flux `flux` (Rusanov/HLLC) and limiter choice `lim`, at step counter parity `par`: one
-// stage with the limiter, the whole step (`stage` ignored) without.
-hipError_t launch_euler_batch(int M, int flux, bool lim, const EulerSet *sets, const int2 *tiles, int ntiles,
-                              int stage, int par, hipStream_t s);
-// Elements a wavefront owns: 64 lanes less the halo on each side (two lanes with the limiter,
-// one per stage of the step without).
-constexpr int kEulerLimOwned = 60, kEulerStepOwned = 58;   // SSP-RK3 (batches)
-// Workgroups for E elements with `owned` elements per wavefront.
-__host__ __device__ inline int euler_blocks(int E, int owned) {
-  const int waves = (E + owned - 1) / owned;
-  return (waves + kEulerBlock / 64 - 1) / (kEulerBlock / 64);
-}
+// One whole time step (`stages` = 3, 2 or 5 RK stages) of the one-step model; `lim` (null = no
+// limiter) adds the limiter of every stage's output.
+hipError_t launch_euler_step(int M, int flux, int stages, const EulerArgs &a, const LimiterArgs *lim, hipStream_t s);
+// Batched one-step SSP-RK3 step over a work list of (instance, block) entries, all of order M, flux
+// `flux` (Rusanov/HLLC) and limiter choice `lim`, at step counter parity `par`.
+hipError_t launch_euler_batch(int M, int flux, bool lim, const EulerSet *sets, const int2 *tiles, int ntiles, int par,
+                              hipStream_t s);
+// Workgroups of the step kernel for E elements.
+int euler_blocks(int E, int stages, bool lim);
 hipError_t launch_to_planes(const double *src, double *dst, int E, int VM, hipStream_t s);
 hipError_t launch_from_planes(const double *src, double *dst, int E, int VM, hipStream_t s);
 

@@ -205,8 +205,8 @@ bool make_layout(const adg_physics *ph, const adg_discretization *d, const adg_a
   (void)visc;
   size_t nstate = state_doubles(L.E, L.V * L.M) * sizeof(double);
   size_t off = 0;
-  // a 2N scheme with the limiter keeps two registers (each stage writes the one it
-  // does not read)
+  // (the one-step model's whole-step kernel alternates between the first two; the size of a
+  // workspace, which callers keep, stays that of one buffer per stage)
   L.nbuf = (d->limiter && ph->model == ADG_ONESTEP && rk_stage(d->rk, 0).two_n) ? 4 : 3;
   L.state = off;  off += L.nbuf * align256(nstate);
   L.flags = off;  off += align256((size_t)L.E);
@@ -252,7 +252,7 @@ adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc
   P.lay = L;
   P.base = base;
   size_t nstate = state_doubles(L.E, L.V * L.M) * sizeof(double);
-  for (int b = 0; b < L.nbuf; ++b) P.W[b] = (double *)(base + L.state + b * align256(nstate));
+  for (int b = 0; b < 3; ++b) P.W[b] = (double *)(base + L.state + b * align256(nstate));
   P.flags = (int8_t *)(base + L.flags);
   P.face_if = (int *)(base + L.face_if);
   P.step = (long long *)(base + L.counters);
@@ -313,17 +313,15 @@ adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc
     a.E = L.E;
     a.periodic = periodic;
     a.store_U = disc->limiter && L.nif > 0;
-    a.kbuf = P.W[2];
-    a.kout = P.W[2];
-    a.alt = !rk_stage(disc->rk, 0).two_n;
-    for (int b = 0; b < 3; ++b) a.W[b] = P.W[b];
-    a.rk = rk_stage(disc->rk, 0);
+    for (int b = 0; b < 2; ++b) a.W[b] = P.W[b];
     a.dt = disc->dt;
     a.two_over_dx = 2.0 / dx;
     a.ph = {phys->gamma, phys->q_heat, phys->e_act, phys->k_pre};
     a.dl = dl;
     a.ring = rp;
-    a.tb = tb;
+    std::memcpy(a.tb.B, tb.B, sizeof tb.B);
+    std::memcpy(a.tb.WG, tb.WG, sizeof tb.WG);
+    std::memcpy(a.tb.WB, tb.WB, sizeof tb.WB);
     if (disc->limiter) {
       LimiterArgs &l = P.la;
       l.flags = P.flags;

@@ -31,7 +31,7 @@ struct Problem {
   adg_async as{};
   Layout lay{};
   char *base = nullptr;
-  double *W[4] = {nullptr, nullptr, nullptr, nullptr};
+  double *W[3] = {nullptr, nullptr, nullptr};
   int8_t *flags = nullptr;
   int *face_if = nullptr;
   long long *step = nullptr;   // [2]: the step counters of the two parities

@@ -1,6 +1,7 @@
 """The one-step model's whole-step kernel at the edges of its wavefront tiles (64 lanes less a halo
-of one lane per RK stage on each side: 58 owned elements for SSP-RK3, 60 for RK2, 54 for the
-five-stage scheme), against the oracle at the repository's parity bound (1e-10)."""
+of one lane per RK stage on each side, two with the limiter: 58 and 52 owned elements for SSP-RK3, 60
+and 56 for RK2, 54 and 44 for the five-stage scheme), against the oracle at the repository's parity
+bound (1e-10)."""
 import pytest
 
 from _parity import check
@@ -40,4 +41,30 @@ def test_whole_step_tiles(adg, orc, rk, E, bc, flux):
     o.step(12)
     check(s.state(), o.state(), case, 1e-10, f"{rk} E={E} {bc}")
     assert s.step_count() == 12
+    s.close()
+
+
+LIMITED = {"ssprk3": 52, "rk2": 56, "lserk4": 44}
+LIM_SIZES = {rk: [1, 2, 3, 5, 2 * {"ssprk3": 3, "rk2": 2, "lserk4": 5}[rk] + 1, n - 1, n, n + 1, 2 * n + 1]
+             for rk, n in LIMITED.items()}
+
+
+@pytest.mark.parametrize("bc", ["periodic", "transmissive"])
+@pytest.mark.parametrize("rk,E", [(rk, E) for rk, sizes in LIM_SIZES.items() for E in sizes])
+def test_whole_step_limiter_tiles(adg, orc, rk, E, bc):
+    """Every cell limited (no threshold that round-off could cross) on the smooth wave, with more delayed
+    interfaces in a wavefront than one round of neighbour slots takes where the mesh allows."""
+    order_p = 1 + (E + 1) % 4
+    case, w0 = gen.case_c0(E=E, order_p=order_p, n_pe=min(E, 11), mode="saa", pmf=(0.3, 0.4, 0.3),
+                           cfl={1: 0.1, 2: 0.05, 3: 0.02, 4: 0.005}[order_p], k_pre=1e2)
+    case["disc"].update(bc=bc, flux="hllc" if E % 2 else "rusanov", rk=rk, limiter=1, indicator="all")
+    s = adg.Solver(case)
+    s.set_state(w0)
+    o = orc.OracleSolver(case, w0, 11)
+    s.step(10)
+    o.step(10)
+    check(s.state(), o.state(), case, 1e-10, f"limited {rk} E={E} {bc}")
+    flags, total = s.flags()
+    stages = {"ssprk3": 3, "rk2": 2, "lserk4": 5}[rk]
+    assert flags.all() and total == 10 * stages * E
     s.close()
