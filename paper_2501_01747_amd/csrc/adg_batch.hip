@@ -466,12 +466,7 @@ adg_status adg_batch_add(adg_batch *b, const adg_physics *phys, const adg_discre
     he = hipMemcpy(b->d_eu + slot, &es, sizeof es, hipMemcpyHostToDevice);
     if (he != hipSuccess) return fail_release(he, "descriptor upload");
   }
-  const int VM = L.V * L.M;
-  if (where == ADG_HOST) he = upload_state_host(P, w0, b->stream);
-  else he = launch_to_planes(w0, P.W[0], L.E, VM, b->stream);
-  if (he == hipSuccess) he = reset_problem(P, b->stream);
-  if (he == hipSuccess) he = launch_zero(P.step, 2 * sizeof(long long), b->stream);
-  if (he == hipSuccess) he = launch_zero(P.err, sizeof(int), b->stream);
+  he = where == ADG_HOST ? set_state_host(P, w0, b->stream) : set_state_device(P, w0, b->stream);
   if (he == hipSuccess) he = hipStreamSynchronize(b->stream);
   if (he != hipSuccess) return fail_release(he, "initial state");
   b->slots[slot] = s;
@@ -536,8 +531,7 @@ adg_status adg_batch_get_state(adg_batch *b, int32_t slot, double *w, int64_t co
   if (!valid_slot(b, slot) || !w) return bfail(b, ADG_ERR_ARG, "no instance in this slot");
   const Problem &P = b->slots[slot].P;
   const Layout &L = P.lay;
-  const int VM = L.V * L.M;
-  if (count != (int64_t)L.E * VM) return bfail(b, ADG_ERR_ARG, "state size mismatch");
+  if (count != (int64_t)L.E * L.V * L.M) return bfail(b, ADG_ERR_ARG, "state size mismatch");
   // one-step instances: the state lives in buffer (step count) mod 2
   const double *src = P.W[0];
   if (P.phys.model == ADG_ONESTEP) {
@@ -547,9 +541,9 @@ adg_status adg_batch_get_state(adg_batch *b, int32_t slot, double *w, int64_t co
     src = P.W[n & 1];
   }
   if (where == ADG_HOST) {
-    BHIP(b, download_state_host(P, src, w, b->stream));
+    BHIP(b, get_state_host(P, src, w, nullptr, b->stream));
   } else if (where == ADG_DEVICE) {
-    BHIP(b, launch_from_planes(src, w, L.E, VM, b->stream));
+    BHIP(b, get_state_device(P, src, w, nullptr, b->stream));
   } else {
     return bfail(b, ADG_ERR_ARG, "where must be ADG_HOST or ADG_DEVICE");
   }

@@ -763,20 +763,6 @@ __global__ __launch_bounds__(64 * kEulerWaves<LIM>, LIM ? (M <= 3 ? 3 : 2) : 1) 
                                    tl.y * kEulerWaves<LIM> + w, n, par);
 }
 
-// caller layout [E][VM] <-> device layout (sidx)
-__global__ void to_planes_kernel(const double *__restrict__ src, double *__restrict__ dst, int E, int VM) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)E * VM) return;
-  const int e = (int)(idx / VM), c = (int)(idx % VM);
-  dst[sidx(e, c, VM)] = src[idx];
-}
-__global__ void from_planes_kernel(const double *__restrict__ src, double *__restrict__ dst, int E, int VM) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)E * VM) return;
-  const int e = (int)(idx / VM), c = (int)(idx % VM);
-  dst[idx] = src[sidx(e, c, VM)];
-}
-
 // ---------------------------------------------------------------- launchers
 
 int euler_blocks(int E, int stages, bool lim) {
@@ -839,18 +825,6 @@ hipError_t launch_euler_batch(int M, int flux, bool lim, const EulerSet *sets, c
     case 5: return batch_M<5>(flux, lim, sets, tiles, ntiles, par, s);
   }
   return hipErrorInvalidValue;
-}
-
-hipError_t launch_to_planes(const double *src, double *dst, int E, int VM, hipStream_t s) {
-  const long long n = (long long)E * VM;
-  hipLaunchKernelGGL(to_planes_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, dst, E, VM);
-  return hipGetLastError();
-}
-
-hipError_t launch_from_planes(const double *src, double *dst, int E, int VM, hipStream_t s) {
-  const long long n = (long long)E * VM;
-  hipLaunchKernelGGL(from_planes_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, dst, E, VM);
-  return hipGetLastError();
 }
 
 }  // namespace adg

@@ -185,7 +185,5 @@ hipError_t launch_euler_batch(int M, int flux, bool lim, const EulerSet *sets, c
                               hipStream_t s);
 // Workgroups of the step kernel for E elements.
 int euler_blocks(int E, int stages, bool lim);
-hipError_t launch_to_planes(const double *src, double *dst, int E, int VM, hipStream_t s);
-hipError_t launch_from_planes(const double *src, double *dst, int E, int VM, hipStream_t s);
 
 }  // namespace adg

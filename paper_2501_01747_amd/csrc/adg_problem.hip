@@ -2,6 +2,7 @@
 // kernel arguments (shared by the single-problem solver and the batch).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -348,70 +349,121 @@ adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc
   return ADG_OK;
 }
 
-hipError_t upload_state_host(const Problem &P, const double *w, hipStream_t st) {
-  const Layout &L = P.lay;
-  const int VM = L.V * L.M;
-  std::vector<double> planes(state_doubles(L.E, VM), 0.0);
-  for (int e = 0; e < L.E; ++e)
-    for (int c = 0; c < VM; ++c) planes[sidx(e, c, VM)] = w[(size_t)e * VM + c];
-  hipError_t e = hipMemcpyAsync(P.W[0], planes.data(), planes.size() * sizeof(double), hipMemcpyHostToDevice, st);
-  if (e != hipSuccess) return e;
-  return hipStreamSynchronize(st);
-}
+// Caller layout [E][VM] <-> device layout (sidx), one workgroup per block of 64 elements through
+// LDS: both sides are then read and written in whole lines (reading one side at a stride of a line per
+// lane took 293 and 270 us per direction at E = 2^22, N_p = 2, 1.0 GB moved; a new state and its
+// read-back around one time step of 512 elements took 44 us with the reset in launches of its own and
+// the error flag copied after the state, 30 now).  The LDS rows are padded to an odd number of doubles,
+// so that a column's reads spread over the banks.
+constexpr int kPlaneThreads = 256;
 
-hipError_t download_state_host(const Problem &P, const double *buf, double *w, hipStream_t st) {
-  const Layout &L = P.lay;
-  const int VM = L.V * L.M;
-  std::vector<double> planes(state_doubles(L.E, VM));
-  hipError_t e = hipMemcpyAsync(planes.data(), buf, planes.size() * sizeof(double), hipMemcpyDeviceToHost, st);
-  if (e != hipSuccess) return e;
-  e = hipStreamSynchronize(st);
-  if (e != hipSuccess) return e;
-  for (int el = 0; el < L.E; ++el)
-    for (int c = 0; c < VM; ++c) w[(size_t)el * VM + c] = planes[sidx(el, c, VM)];
-  return hipSuccess;
-}
-
-// Zero fill by a kernel (not hipMemsetAsync): a caller may capture the reset of a problem into
-// a HIP graph, and fill kernels replay like any other node.  Eight-byte words where the region
-// is 8-byte aligned and long, single bytes otherwise (per-slot counters of a batch are 4-byte
-// aligned).
-__global__ void zero_words_kernel(unsigned long long *__restrict__ p, size_t nwords, unsigned char *__restrict__ tail,
-                                  int ntail) {
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nwords; i += stride) p[i] = 0ull;
-  if (blockIdx.x == 0 && (int)threadIdx.x < ntail) tail[threadIdx.x] = 0;
-}
-
-__global__ void zero_bytes_kernel(unsigned char *__restrict__ p, size_t n) {
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0;
-}
-
-hipError_t launch_zero(void *p, size_t bytes, hipStream_t st) {
-  if (bytes == 0) return hipSuccess;
-  const int threads = 256;
-  if (((uintptr_t)p & 7) || bytes < 64) {
-    size_t blocks = (bytes + threads - 1) / threads;
-    if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(zero_bytes_kernel, dim3((unsigned)blocks), dim3(threads), 0, st, (unsigned char *)p, bytes);
-    return hipGetLastError();
+__device__ __forceinline__ void to_planes_block(const double *__restrict__ src, double *__restrict__ dst, int E, int VM,
+                                                int blk, double *lds) {
+  const int ne = min(kLayoutBlock, E - blk * kLayoutBlock), row = VM | 1;
+  const double *s = src + (size_t)blk * kLayoutBlock * VM;
+  double *d = dst + (size_t)blk * kLayoutBlock * VM;
+  for (int i = threadIdx.x; i < ne * VM; i += kPlaneThreads) lds[i / VM * row + i % VM] = s[i];
+  __syncthreads();
+  for (int i = threadIdx.x; i < kLayoutBlock * VM; i += kPlaneThreads) {
+    const int e = i % kLayoutBlock, c = i / kLayoutBlock;
+    if (e < ne) d[i] = lds[e * row + c];
   }
-  const size_t nwords = bytes / 8;
-  size_t blocks = (nwords + threads - 1) / threads;
-  if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)blocks), dim3(threads), 0, st, (unsigned long long *)p, nwords,
-                     (unsigned char *)p + nwords * 8, (int)(bytes % 8));
+}
+
+// What a new state resets: the step counters, the error flag, and regions of whole 8-byte words.
+struct Reset {
+  long long *step;
+  int *err;
+  unsigned long long *p[3];
+  size_t words[3];
+};
+
+// A new state: the first `blocks` workgroups change its layout, the others clear what it resets (a
+// kernel, not hipMemsetAsync: a caller may capture it into a HIP graph).
+__global__ __launch_bounds__(kPlaneThreads) void set_state_kernel(const double *__restrict__ src, double *__restrict__ dst,
+                                                                 int E, int VM, int blocks, Reset z) {
+  extern __shared__ double lds[];
+  if ((int)blockIdx.x < blocks) {
+    to_planes_block(src, dst, E, VM, blockIdx.x, lds);
+    return;
+  }
+  const size_t b = blockIdx.x - blocks, stride = (size_t)(gridDim.x - blocks) * kPlaneThreads;
+  for (int r = 0; r < 3; ++r)
+    for (size_t i = b * kPlaneThreads + threadIdx.x; i < z.words[r]; i += stride) z.p[r][i] = 0ull;
+  if (b == 0 && threadIdx.x == 0) {
+    z.step[0] = 0;
+    z.step[1] = 0;
+    *z.err = 0;
+  }
+}
+
+// The state in the caller's layout, and the error flag beside it (err_out, may be null).
+__global__ __launch_bounds__(kPlaneThreads) void get_state_kernel(const double *__restrict__ src, double *__restrict__ dst,
+                                                                 int E, int VM, const int *err, int *err_out) {
+  extern __shared__ double lds[];
+  const int blk = blockIdx.x;
+  const int ne = min(kLayoutBlock, E - blk * kLayoutBlock), row = VM | 1;
+  const double *s = src + (size_t)blk * kLayoutBlock * VM;
+  double *d = dst + (size_t)blk * kLayoutBlock * VM;
+  for (int i = threadIdx.x; i < kLayoutBlock * VM; i += kPlaneThreads) {
+    const int e = i % kLayoutBlock, c = i / kLayoutBlock;
+    if (e < ne) lds[e * row + c] = s[i];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < ne * VM; i += kPlaneThreads) d[i] = lds[i / VM * row + i % VM];
+  if (blk == 0 && threadIdx.x == 0 && err_out) *err_out = *err;
+}
+
+static size_t plane_lds(int VM) { return sizeof(double) * kLayoutBlock * (size_t)(VM | 1); }
+
+hipError_t set_state_device(const Problem &P, const double *w, hipStream_t st) {
+  const Layout &L = P.lay;
+  const int VM = L.V * L.M, blocks = (L.E + kLayoutBlock - 1) / kLayoutBlock;
+  Reset z{};
+  z.step = P.step;
+  z.err = P.err;
+  // each region is a whole number of 256-byte units in the workspace
+  z.p[0] = (unsigned long long *)(P.base + L.counters);
+  z.words[0] = 256 / 8;
+  z.p[1] = (unsigned long long *)P.ring;
+  z.words[1] = (size_t)L.D * L.S * (L.nif > 0 ? L.nif : 1) * L.rec;
+  z.p[2] = (unsigned long long *)P.flags;
+  z.words[2] = ((size_t)L.E + 7) / 8;
+  const size_t words = z.words[0] + z.words[1] + z.words[2];
+  const int clear = (int)std::min<size_t>(512, (words + 4 * kPlaneThreads - 1) / (4 * kPlaneThreads));
+  hipLaunchKernelGGL(set_state_kernel, dim3(blocks + clear), dim3(kPlaneThreads), plane_lds(VM), st, w, P.W[0], L.E, VM,
+                     blocks, z);
   return hipGetLastError();
 }
 
-hipError_t reset_problem(const Problem &P, hipStream_t st) {
+hipError_t get_state_device(const Problem &P, const double *buf, double *w, int *err_out, hipStream_t st) {
   const Layout &L = P.lay;
-  hipError_t e = launch_zero(P.base + L.counters, 256, st);
-  if (e == hipSuccess)
-    e = launch_zero(P.ring, sizeof(double) * (size_t)L.D * L.S * (L.nif > 0 ? L.nif : 1) * L.rec, st);
-  if (e == hipSuccess) e = launch_zero(P.flags, (size_t)L.E, st);
-  return e;
+  const int VM = L.V * L.M, blocks = (L.E + kLayoutBlock - 1) / kLayoutBlock;
+  hipLaunchKernelGGL(get_state_kernel, dim3(blocks), dim3(kPlaneThreads), plane_lds(VM), st, buf, w, L.E, VM, P.err, err_out);
+  return hipGetLastError();
+}
+
+// Host states change their layout on the device, through a state buffer that is free between steps.
+static double *free_buffer(const Problem &P, const double *state) {
+  return P.phys.model == ADG_ONESTEP ? P.W[2] : state == P.W[1] ? P.W[0] : P.W[1];
+}
+
+hipError_t set_state_host(const Problem &P, const double *w, hipStream_t st) {
+  double *buf = free_buffer(P, P.W[0]);
+  const size_t bytes = sizeof(double) * (size_t)P.lay.E * P.lay.V * P.lay.M;
+  hipError_t e = hipMemcpyAsync(buf, w, bytes, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = set_state_device(P, buf, st);
+  const hipError_t done = hipStreamSynchronize(st);   // w is the caller's: not read after the return
+  return e == hipSuccess ? done : e;
+}
+
+hipError_t get_state_host(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st) {
+  double *buf = free_buffer(P, state);
+  const size_t bytes = sizeof(double) * (size_t)P.lay.E * P.lay.V * P.lay.M;
+  hipError_t e = get_state_device(P, state, buf, err_out, st);
+  if (e == hipSuccess) e = hipMemcpyAsync(w, buf, bytes, hipMemcpyDeviceToHost, st);
+  const hipError_t done = hipStreamSynchronize(st);
+  return e == hipSuccess ? done : e;
 }
 
 }  // namespace adg

@@ -56,11 +56,13 @@ adg_status check_precision(const adg_physics *ph, const adg_discretization *d, s
 // constant data and fills the kernel arguments.
 adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc, const adg_async *as, char *base,
                          const Layout &L, Problem &P);
-hipError_t upload_state_host(const Problem &P, const double *w, hipStream_t st);
-hipError_t download_state_host(const Problem &P, const double *buf, double *w, hipStream_t st);
-// Step counter, error flag, history ring and flags back to zero.
-hipError_t reset_problem(const Problem &P, hipStream_t st);
-// Zero `bytes` bytes at p with a fill kernel on stream st (capturable, unlike hipMemsetAsync).
-hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
+// A new state w ([E][V][M]) in W[0], the step counters, error flag, history ring and flags back to
+// zero: one launch, enqueued (capturable); the host form copies w first and waits.
+hipError_t set_state_device(const Problem &P, const double *w, hipStream_t st);
+hipError_t set_state_host(const Problem &P, const double *w, hipStream_t st);
+// The state in buffer `state` (one of P.W) in the caller's layout, and the error flag in *err_out
+// (device-accessible; null: not reported): enqueued; the host form waits.
+hipError_t get_state_device(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st);
+hipError_t get_state_host(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st);
 
 }  // namespace adg
