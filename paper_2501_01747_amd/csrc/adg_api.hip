@@ -224,7 +224,9 @@ adg_status adg_create(const adg_physics *phys, const adg_discretization *disc, c
     return create_fail(ADG_ERR_ARG, "workspace must be a non-null 256-byte aligned device pointer");
   if (workspace_bytes < L.total) return create_fail(ADG_ERR_NOMEM, "workspace smaller than adg_workspace_bytes()");
   adg_solver *s = new adg_solver();
-  adg_status rc = setup_problem(phys, disc, as, (char *)device_workspace, L, s->P);
+  std::vector<int> faces;
+  adg_status rc = setup_problem(phys, disc, as, (char *)device_workspace, L, s->P, faces);
+  if (rc == ADG_OK) rc = upload_problem(s->P, faces);
   if (rc != ADG_OK) { delete s; return create_fail(rc, "problem set-up failed (unsupported combination or HIP error)"); }
   s->stream = (hipStream_t)hip_stream;
   // about 25 us once for a solver, 6 to 10 us saved on each adg_get_state
@@ -262,7 +264,9 @@ adg_status adg_create_noalloc(const adg_physics *phys, const adg_discretization 
     return create_fail(ADG_ERR_STATE, "a solver of adg_create_noalloc is alive on this device (destroy it first)");
   adg_solver *s = &g_noalloc_solver[dev];
   *s = adg_solver();
-  adg_status rc = setup_problem(phys, disc, as, (char *)g_scratch_ptr[dev], L, s->P);
+  std::vector<int> faces;
+  adg_status rc = setup_problem(phys, disc, as, (char *)g_scratch_ptr[dev], L, s->P, faces);
+  if (rc == ADG_OK) rc = upload_problem(s->P, faces);
   if (rc != ADG_OK) return create_fail(rc, "problem set-up failed (unsupported combination or HIP error)");
   s->stream = (hipStream_t)hip_stream;
   s->noalloc_dev = dev;

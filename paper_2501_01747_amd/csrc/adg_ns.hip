@@ -871,14 +871,15 @@ static adg_status upload_mech(const adg_physics *ph, void *dev_mech) {
   return ADG_OK;
 }
 
-adg_status ns_setup(NsArgs &a, const adg_physics *ph, const adg_discretization *d, int E, int M, bool periodic,
-                    double dx, const DelayParams &dl, const RingParams &rp, const Tables &tb, const int *face_if,
-                    long long *step, int *err, void *dev_mech) {
-  const int ns = ph->mech->n_species;
-  const adg_status rc = ns_capacity(ns) == kNsMaxSpecies ? upload_mech<kNsMaxSpecies>(ph, dev_mech)
-                                                         : upload_mech<kNsWideSpecies>(ph, dev_mech);
-  if (rc != ADG_OK) return rc;
-  a.ns = ns;
+adg_status ns_upload_mech(const adg_physics *ph, void *dev_mech) {
+  return ns_capacity(ph->mech->n_species) == kNsMaxSpecies ? upload_mech<kNsMaxSpecies>(ph, dev_mech)
+                                                           : upload_mech<kNsWideSpecies>(ph, dev_mech);
+}
+
+void ns_setup(NsArgs &a, const adg_physics *ph, const adg_discretization *d, int E, int M, bool periodic,
+              double dx, const DelayParams &dl, const RingParams &rp, const Tables &tb, const int *face_if,
+              long long *step, int *err, void *dev_mech) {
+  a.ns = ph->mech->n_species;
   a.periodic = periodic ? 1 : 0;
   a.at_in = nullptr;
   a.at_out = nullptr;
@@ -895,7 +896,6 @@ adg_status ns_setup(NsArgs &a, const adg_physics *ph, const adg_discretization *
   a.ring = rp;
   a.tb = tb;
   a.M = M;
-  return ADG_OK;
 }
 
 template <int NSC>

@@ -114,9 +114,11 @@ struct NsArgs {
 bool ns_supported(int n_species, int n_reactions);
 // Bytes of the device mechanism of a problem with n_species species.
 size_t ns_mech_bytes(int n_species);
-adg_status ns_setup(NsArgs &a, const adg_physics *ph, const adg_discretization *d, int E, int M, bool periodic,
-                    double dx, const DelayParams &dl, const RingParams &rp, const Tables &tb, const int *face_if,
-                    long long *step, int *err, void *dev_mech);
+void ns_setup(NsArgs &a, const adg_physics *ph, const adg_discretization *d, int E, int M, bool periodic,
+              double dx, const DelayParams &dl, const RingParams &rp, const Tables &tb, const int *face_if,
+              long long *step, int *err, void *dev_mech);
+// The device form of a mechanism to dev_mech (waits; validates the mechanism).
+adg_status ns_upload_mech(const adg_physics *ph, void *dev_mech);
 // The device form of a mechanism (host side; validates it).
 template <int NSC>
 adg_status ns_build_mech(const adg_physics *ph, NsMechT<NSC> &hm);

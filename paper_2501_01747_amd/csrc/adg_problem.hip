@@ -237,7 +237,7 @@ adg_status check_precision(const adg_physics *ph, const adg_discretization *d, s
 }
 
 adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc, const adg_async *as, char *base,
-                         const Layout &L, Problem &P) {
+                         const Layout &L, Problem &P, std::vector<int> &faces) {
   if (phys->model == ADG_DETAILED && !ns_supported(phys->n_species, phys->mech->n_reactions))
     return ADG_ERR_UNSUPPORTED;
   std::vector<int32_t> off(as->n_pe + 1);
@@ -266,15 +266,13 @@ adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc
   }
 
   const bool periodic = disc->bc == ADG_PERIODIC;
-  std::vector<int> fif(L.E + 1, -1);
+  faces.assign(L.E + 1, -1);
   if (periodic) {
-    for (int p = 0; p < as->n_pe; ++p) fif[off[p]] = p;
-    fif[L.E] = fif[0];
+    for (int p = 0; p < as->n_pe; ++p) faces[off[p]] = p;
+    faces[L.E] = faces[0];
   } else {
-    for (int p = 1; p < as->n_pe; ++p) fif[off[p]] = p - 1;
+    for (int p = 1; p < as->n_pe; ++p) faces[off[p]] = p - 1;
   }
-  if (hipMemcpy(P.face_if, fif.data(), sizeof(int) * (L.E + 1), hipMemcpyHostToDevice) != hipSuccess)
-    return ADG_ERR_HIP;
 
   DelayParams dl{};
   dl.mode = as->mode;
@@ -290,8 +288,6 @@ adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc
   if (as->mode == ADG_SCHEDULE) {
     dl.sched = (const int8_t *)(base + L.sched);
     dl.sched_steps = as->schedule_steps;
-    if (hipMemcpy(base + L.sched, as->schedule, (size_t)as->schedule_steps * L.nif, hipMemcpyHostToDevice) != hipSuccess)
-      return ADG_ERR_HIP;
   }
   RingParams rp{};
   rp.base = P.ring;
@@ -335,9 +331,7 @@ adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc
       build_limiter_tables(L.M, l);
     }
   } else {
-    adg_status rc = ns_setup(P.na, phys, disc, L.E, L.M, periodic, dx, dl, rp, tb, P.face_if, P.step, P.err,
-                             (void *)(base + L.mech));
-    if (rc != ADG_OK) return rc;
+    ns_setup(P.na, phys, disc, L.E, L.M, periodic, dx, dl, rp, tb, P.face_if, P.step, P.err, (void *)(base + L.mech));
     for (int b = 0; b < 3; ++b) P.na.W[b] = P.W[b];
     P.na.kbuf = P.W[2];
     P.na.rk = rk_stage(disc->rk, 0);
@@ -347,6 +341,16 @@ adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc
     P.na.at_out = nullptr;
   }
   return ADG_OK;
+}
+
+adg_status upload_problem(const Problem &P, const std::vector<int> &faces) {
+  const Layout &L = P.lay;
+  if (hipMemcpy(P.face_if, faces.data(), sizeof(int) * faces.size(), hipMemcpyHostToDevice) != hipSuccess)
+    return ADG_ERR_HIP;
+  if (P.as.mode == ADG_SCHEDULE && hipMemcpy(P.base + L.sched, P.as.schedule, (size_t)P.as.schedule_steps * L.nif,
+                                             hipMemcpyHostToDevice) != hipSuccess)
+    return ADG_ERR_HIP;
+  return P.phys.model == ADG_DETAILED ? ns_upload_mech(&P.phys, P.base + L.mech) : ADG_OK;
 }
 
 // Caller layout [E][VM] <-> device layout (sidx), one workgroup per block of 64 elements through
@@ -370,13 +374,32 @@ __device__ __forceinline__ void to_planes_block(const double *__restrict__ src, 
   }
 }
 
-// What a new state resets: the step counters, the error flag, and regions of whole 8-byte words.
+// What a new state resets: the step counters, the error flag, and regions of whole 8-byte words; and
+// what is copied along with it.
 struct Reset {
   long long *step;
   int *err;
   unsigned long long *p[3];
   size_t words[3];
+  Copies cp;
 };
+
+__device__ __forceinline__ void copy_words(const Copies &c, size_t i0, size_t stride) {
+  for (int r = 0; r < kCopies; ++r)
+    for (size_t i = i0; i < c.words[r]; i += stride) c.dst[r][i] = c.src[r][i];
+}
+
+__global__ __launch_bounds__(kPlaneThreads) void copy_kernel(Copies c) {
+  copy_words(c, (size_t)blockIdx.x * kPlaneThreads + threadIdx.x, (size_t)gridDim.x * kPlaneThreads);
+}
+
+hipError_t launch_copies(const Copies &c, hipStream_t st) {
+  size_t most = 1;
+  for (int r = 0; r < kCopies; ++r) most = std::max(most, c.words[r]);
+  hipLaunchKernelGGL(copy_kernel, dim3((unsigned)std::min<size_t>(64, (most + kPlaneThreads - 1) / kPlaneThreads)),
+                     dim3(kPlaneThreads), 0, st, c);
+  return hipGetLastError();
+}
 
 // A new state: the first `blocks` workgroups change its layout, the others clear what it resets (a
 // kernel, not hipMemsetAsync: a caller may capture it into a HIP graph).
@@ -390,6 +413,7 @@ __global__ __launch_bounds__(kPlaneThreads) void set_state_kernel(const double *
   const size_t b = blockIdx.x - blocks, stride = (size_t)(gridDim.x - blocks) * kPlaneThreads;
   for (int r = 0; r < 3; ++r)
     for (size_t i = b * kPlaneThreads + threadIdx.x; i < z.words[r]; i += stride) z.p[r][i] = 0ull;
+  copy_words(z.cp, b * kPlaneThreads + threadIdx.x, stride);
   if (b == 0 && threadIdx.x == 0) {
     z.step[0] = 0;
     z.step[1] = 0;
@@ -416,7 +440,7 @@ __global__ __launch_bounds__(kPlaneThreads) void get_state_kernel(const double *
 
 static size_t plane_lds(int VM) { return sizeof(double) * kLayoutBlock * (size_t)(VM | 1); }
 
-hipError_t set_state_device(const Problem &P, const double *w, hipStream_t st) {
+hipError_t set_state_device(const Problem &P, const double *w, hipStream_t st, const Copies *copies) {
   const Layout &L = P.lay;
   const int VM = L.V * L.M, blocks = (L.E + kLayoutBlock - 1) / kLayoutBlock;
   Reset z{};
@@ -429,7 +453,11 @@ hipError_t set_state_device(const Problem &P, const double *w, hipStream_t st) {
   z.words[1] = (size_t)L.D * L.S * (L.nif > 0 ? L.nif : 1) * L.rec;
   z.p[2] = (unsigned long long *)P.flags;
   z.words[2] = ((size_t)L.E + 7) / 8;
-  const size_t words = z.words[0] + z.words[1] + z.words[2];
+  size_t words = z.words[0] + z.words[1] + z.words[2];
+  if (copies) {
+    z.cp = *copies;
+    for (int r = 0; r < kCopies; ++r) words += z.cp.words[r] / 2;
+  }
   const int clear = (int)std::min<size_t>(512, (words + 4 * kPlaneThreads - 1) / (4 * kPlaneThreads));
   hipLaunchKernelGGL(set_state_kernel, dim3(blocks + clear), dim3(kPlaneThreads), plane_lds(VM), st, w, P.W[0], L.E, VM,
                      blocks, z);
@@ -448,11 +476,11 @@ static double *free_buffer(const Problem &P, const double *state) {
   return P.phys.model == ADG_ONESTEP ? P.W[2] : state == P.W[1] ? P.W[0] : P.W[1];
 }
 
-hipError_t set_state_host(const Problem &P, const double *w, hipStream_t st) {
+hipError_t set_state_host(const Problem &P, const double *w, hipStream_t st, const Copies *copies) {
   double *buf = free_buffer(P, P.W[0]);
   const size_t bytes = sizeof(double) * (size_t)P.lay.E * P.lay.V * P.lay.M;
   hipError_t e = hipMemcpyAsync(buf, w, bytes, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = set_state_device(P, buf, st);
+  if (e == hipSuccess) e = set_state_device(P, buf, st, copies);
   const hipError_t done = hipStreamSynchronize(st);   // w is the caller's: not read after the return
   return e == hipSuccess ? done : e;
 }

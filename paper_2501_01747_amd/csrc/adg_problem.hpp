@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <string>
+#include <vector>
 
 #include "adg.h"
 #include "adg_internal.hpp"
@@ -52,14 +53,24 @@ bool make_layout(const adg_physics *ph, const adg_discretization *d, const adg_a
 // ADG_ERR_UNSUPPORTED for precisions a single problem cannot run (MIXED_BF16; MIXED_FP32 with
 // the one-step model), with the reason in *why.
 adg_status check_precision(const adg_physics *ph, const adg_discretization *d, std::string *why);
-// Places the problem at `base` (256-byte aligned, L.total bytes), uploads its
-// constant data and fills the kernel arguments.
+// Places the problem at `base` (256-byte aligned, L.total bytes), fills the kernel arguments and the
+// interface index of every face (no device work).
 adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc, const adg_async *as, char *base,
-                         const Layout &L, Problem &P);
+                         const Layout &L, Problem &P, std::vector<int> &faces);
+// Its constant data to the device: the faces, the schedule and the mechanism (waits).
+adg_status upload_problem(const Problem &P, const std::vector<int> &faces);
+// Up to kCopies regions of 4-byte words for one launch to copy (either side may be pinned host memory).
+constexpr int kCopies = 3;
+struct Copies {
+  const unsigned *src[kCopies];
+  unsigned *dst[kCopies];
+  size_t words[kCopies];
+};
+hipError_t launch_copies(const Copies &c, hipStream_t st);
 // A new state w ([E][V][M]) in W[0], the step counters, error flag, history ring and flags back to
-// zero: one launch, enqueued (capturable); the host form copies w first and waits.
-hipError_t set_state_device(const Problem &P, const double *w, hipStream_t st);
-hipError_t set_state_host(const Problem &P, const double *w, hipStream_t st);
+// zero, with `copies` in the same launch: enqueued (capturable); the host form copies w first and waits.
+hipError_t set_state_device(const Problem &P, const double *w, hipStream_t st, const Copies *copies = nullptr);
+hipError_t set_state_host(const Problem &P, const double *w, hipStream_t st, const Copies *copies = nullptr);
 // The state in buffer `state` (one of P.W) in the caller's layout, and the error flag in *err_out
 // (device-accessible; null: not reported): enqueued; the host form waits.
 hipError_t get_state_device(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st);

@@ -3,6 +3,7 @@ from host and device memory; and the reset that goes with a new state."""
 import numpy as np
 import pytest
 
+from _parity import check
 from test_gpu_ns import mechanism_of
 from workloads import gen
 
@@ -69,3 +70,30 @@ def test_new_state_starts_over(adg, model):
     assert np.array_equal(s.state(), ref.state())
     s.close()
     ref.close()
+
+
+@pytest.mark.parametrize("graph_steps", [0, 3])
+def test_batch_instances_at_their_own_counts(adg, orc, graph_steps):
+    """One-step instances admitted at odd and even batch steps, one by a schedule of delays, one that stops
+    at an odd count, each read after steps with and without graphs: the host knows which buffer is theirs."""
+    sched = (np.arange(64 * 5, dtype=np.int8).reshape(64, 5) % 2).copy()
+    specs = [dict(n_pe=5), dict(n_pe=5, mode="schedule", schedule=sched), dict(n_pe=3), dict(n_pe=4)]
+    cases = [gen.case_c0(E=66 + 7 * i, order_p=2, pmf=(0.3, 0.4, 0.3), **{k: v for k, v in sp.items() if k != "schedule"})
+             for i, sp in enumerate(specs)]
+    cases[1][0]["async"].update(schedule=sched, L=2)
+    targets = [0, 0, 5, 0]
+    heap = sum(adg.Batch.instance_bytes(c) for c, _ in cases)
+    b = adg.Batch(4, sum(c["disc"]["n_elem"] for c, _ in cases), heap)
+    b.set_graph(graph_steps)
+    slots, counts = [], []
+    for (c, w), t in zip(cases, targets):
+        slots.append(b.add(c, w, t))
+        counts.append(0)
+        b.step(7)
+        counts = [min(n + 7, t or 999) for n, t in zip(counts, targets)]
+        for (cc, ww), sl, n in zip(cases, slots, counts):
+            o = orc.OracleSolver(cc, ww, 40)
+            o.step(n)
+            check(b.state(sl), o.state(), cc, 1e-10, f"after {n} steps")
+    assert [int(x) for x in b.poll()[0]] == counts
+    b.close()
