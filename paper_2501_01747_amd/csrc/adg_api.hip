@@ -51,6 +51,7 @@ struct adg_solver {
   std::vector<hipEvent_t> prof_events;
   std::string msg;
   int *host_err = nullptr;   // pinned: the error flag as adg_get_state's kernel stores it (null: copied instead)
+  int reads = 0;             // states read so far, up to 2
   int noalloc_dev = -1;   // device whose static scratch holds this solver (adg_create_noalloc), else -1
 };
 
@@ -229,11 +230,6 @@ adg_status adg_create(const adg_physics *phys, const adg_discretization *disc, c
   if (rc == ADG_OK) rc = upload_problem(s->P, faces);
   if (rc != ADG_OK) { delete s; return create_fail(rc, "problem set-up failed (unsupported combination or HIP error)"); }
   s->stream = (hipStream_t)hip_stream;
-  // about 25 us once for a solver, 6 to 10 us saved on each adg_get_state
-  if (hipHostMalloc((void **)&s->host_err, sizeof(int), hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    s->host_err = nullptr;
-  }
   *out = s;
   return ADG_OK;
 }
@@ -345,8 +341,15 @@ adg_status adg_get_state(adg_solver *s, double *w, int64_t count, int32_t where)
   if (!s || !w) return ADG_ERR_ARG;
   const Layout &L = s->P.lay;
   if (count != (int64_t)L.E * L.V * L.M) return fail(s, ADG_ERR_ARG, "state size mismatch");
-  // the kernel that changes the layout stores the error flag in pinned host memory, so one wait
-  // gives both
+  // From the second read on, the kernel that changes the layout stores the error flag in pinned host
+  // memory, so one wait gives both: 6 to 10 us less for each read, but 25 us and more (250 in a process
+  // that has just freed memory) to allocate, which a state that is read once would not earn back.
+  if (!s->host_err && s->noalloc_dev < 0 && s->reads == 1 &&
+      hipHostMalloc((void **)&s->host_err, sizeof(int), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    s->host_err = nullptr;
+  }
+  s->reads = std::min(s->reads + 1, 2);
   if (where == ADG_HOST) {
     HIP_TRY(s, get_state_host(s->P, s->P.W[s->cur], w, s->host_err, s->stream));
   } else if (where == ADG_DEVICE) {

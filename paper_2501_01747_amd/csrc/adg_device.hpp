@@ -108,6 +108,55 @@ __device__ __forceinline__ void advance_step(long long *step, int par, long long
   if (first_workgroup && threadIdx.x == 0) step[par ^ 1] = n + 1;
 }
 
+// ---------------------------------------------------------------- elementary functions
+// ln 2 to 42 bits (its product with an exponent is exact) and the rest.
+constexpr double kLn2Hi = 0x1.62e42fefa3800p-1, kLn2Lo = 0x1.ef35793c76730p-45, kInvLn2 = 1.4426950408889634;
+
+// exp(x): k = rint(x / ln 2), r = x - k ln 2 in two parts, the Taylor polynomial of degree 13 in
+// |r| <= ln(2)/2 (its remainder is below 2^-57 of the result), 2^k by ldexp, which saturates to 0
+// and infinity.  For finite arguments.
+__device__ __forceinline__ double exp_taylor(double x) {
+  const double k = __builtin_rint(x * kInvLn2);
+  double r = fma(k, -kLn2Hi, x);
+  r = fma(k, -kLn2Lo, r);
+  double p = 1.0 / 6227020800.0;
+  p = fma(p, r, 1.0 / 479001600.0);
+  p = fma(p, r, 1.0 / 39916800.0);
+  p = fma(p, r, 1.0 / 3628800.0);
+  p = fma(p, r, 1.0 / 362880.0);
+  p = fma(p, r, 1.0 / 40320.0);
+  p = fma(p, r, 1.0 / 5040.0);
+  p = fma(p, r, 1.0 / 720.0);
+  p = fma(p, r, 1.0 / 120.0);
+  p = fma(p, r, 1.0 / 24.0);
+  p = fma(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p, r, 1.0);
+  p = fma(p, r, 1.0);
+  return __builtin_amdgcn_ldexp(p, (int)k);
+}
+
+// 1/x by the hardware estimate and two Newton steps, for x away from the ends of the range.
+__device__ __forceinline__ double recip(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+
+// Square root of a positive x from the hardware's estimate of 1/sqrt(x): two coupled Newton steps for
+// the root g and half its reciprocal h, then the remainder x - g^2 folded in.
+__device__ __forceinline__ double root(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  r = fma(-g, g, x);
+  g = fma(r, h, g);
+  r = fma(-g, g, x);
+  return fma(r, h, g);
+}
+
 // ---------------------------------------------------------------- one-step model
 struct Prim1 {
   double rho, u, p, T, a;
@@ -116,11 +165,11 @@ struct Prim1 {
 // rho E = rho u^2/2 + p/(gamma-1) + q rho Y_R;  T = p/rho (R = 1).
 __device__ __forceinline__ bool prim1(const OneStep &ph, const double *w, Prim1 &pr) {
   pr.rho = w[0];
-  const double rinv = 1.0 / pr.rho;
+  const double rinv = recip(pr.rho);
   pr.u = w[1] * rinv;
   pr.p = (ph.gamma - 1.0) * (w[2] - 0.5 * w[1] * pr.u - ph.q_heat * w[3]);
   pr.T = pr.p * rinv;
-  pr.a = sqrt(ph.gamma * pr.T);
+  pr.a = root(ph.gamma * pr.T);
   return pr.rho > 0.0 && pr.p > 0.0 && isfinite(pr.p) && isfinite(pr.rho);
 }
 
@@ -158,20 +207,21 @@ __device__ __forceinline__ bool hllc1(const OneStep &ph, const double *wm, const
   if (SR <= 0.0) { flux1(wp, pp, f); return ok; }
   double num = pp.p - pm.p + pm.rho * pm.u * (SL - pm.u) - pp.rho * pp.u * (SR - pp.u);
   double den = pm.rho * (SL - pm.u) - pp.rho * (SR - pp.u);
-  double Ss = num / den;
+  double Ss = num * recip(den);
   const bool left = Ss >= 0.0;
   const double *wk = left ? wm : wp;
   const Prim1 &pk = left ? pm : pp;
   const double Sk = left ? SL : SR;
   double fk[5];
   flux1(wk, pk, fk);
-  double fac = pk.rho * (Sk - pk.u) / (Sk - Ss);
+  // w* = c (rho, rho Ss, E + (Ss - u)(rho Ss + p/(Sk - u)), rho Y), c = (Sk - u)/(Sk - Ss)
+  const double du = Sk - pk.u, c = du * recip(Sk - Ss);
   double ws[5];
-  ws[0] = fac;
-  ws[1] = fac * Ss;
-  ws[2] = fac * (wk[2] / pk.rho + (Ss - pk.u) * (Ss + pk.p / (pk.rho * (Sk - pk.u))));
-  ws[3] = fac * (wk[3] / pk.rho);
-  ws[4] = fac * (wk[4] / pk.rho);
+  ws[0] = c * pk.rho;
+  ws[1] = ws[0] * Ss;
+  ws[2] = c * (wk[2] + (Ss - pk.u) * (pk.rho * Ss + pk.p * recip(du)));
+  ws[3] = c * wk[3];
+  ws[4] = c * wk[4];
 #pragma unroll
   for (int v = 0; v < 5; ++v) f[v] = fk[v] + Sk * (ws[v] - wk[v]);
   return ok;

@@ -441,14 +441,17 @@ constexpr int owned_lanes() { return 64 - 2 * S * (LIM ? 2 : 1); }
 // of 64 lanes for SSP-RK3, 12 with the limiter).  Past levels' fluxes and boundary-element outputs are
 // all that a delayed face reads from the ring, and those precede the step, so they are gathered for
 // every stage at the start, beside the state loads, and kept in LDS.
-//   Without the limiter, N_p = 2, against one launch per stage: 11.3 us per step against 21.7 at
-// E = 512 (launch and latency bound), 0.33 ms against 0.78 at E = 2^22 (was bound by HBM at 5.2 TB/s;
-// now by the FP64 issue rate, 3.0 TB/s of the one read and one write).
+//   Without the limiter, N_p = 2, against one launch per stage: 9.6 us per step against 21.7 at
+// E = 512 (launch and latency bound), 0.26 ms against 0.78 at E = 2^22 (was bound by HBM at 5.2 TB/s;
+// now by the FP64 issue rate, 3.8 TB/s of the one read and one write).  Instructions decide both, so
+// the Legendre values that are 0 or 1 are left out, the factors of dt L are folded into one per mode,
+// and recip, root and exp_taylor stand for the general division, square root and exponential (0.33 ms
+// and 11.1 us without that).
 //   With it the wavefront stages its unlimited outputs in LDS, and the lanes w s + 2 .. 61 - w s run the
 // indicator and, if troubled, the WENO reconstruction from them; their limited values return to
 // registers.  No other wavefront's data is needed, so wavefronts never wait for each other.  Against one
-// launch per stage: 27 us per step against 52 at E = 8192, N_p = 3 (latency bound), 165 against 240 at
-// E = 10^6, N_p = 2 (HBM bound before; now 70 % of the VALU issue slots).  Registers decide the latter:
+// launch per stage: 25 us per step against 52 at E = 8192, N_p = 3 (latency bound), 147 against 240 at
+// E = 10^6, N_p = 2 (HBM bound before; now by the VALU issue slots).  Registers decide the latter:
 // with w^n held through the limiter 160 bytes per lane went to scratch, three times the step's own
 // writes, and the step took 275 us.
 template <int M, int FLUX, int S, bool LIM>
@@ -543,7 +546,6 @@ __device__ __forceinline__ void euler_step_body(const EulerArgs &a, const Limite
     for (int s = 0; s < S; ++s) {
       const RkStage rk = rk_stage(RK, s);
       const double ca = rk.ca, cb = rk.cb;
-      const bool use_prev = s > 0;
       // the lanes whose output a later stage or the store needs
       const bool calc = lane > W * s && lane < 63 - W * s && (periodic ? xu <= E + H - 2 - W * s : inside);
       double wl[V], wr[V], F[V], Fl[V];
@@ -597,22 +599,25 @@ __device__ __forceinline__ void euler_step_body(const EulerArgs &a, const Limite
           double wq[V];
 #pragma unroll
           for (int v = 0; v < V; ++v) {
-            double acc = 0.0;
+            double acc = u[v][0];   // P_0 = 1
 #pragma unroll
-            for (int j = 0; j < M; ++j) acc += u[v][j] * a.tb.B[q][j];
+            for (int j = 1; j < M; ++j) acc += u[v][j] * a.tb.B[q][j];
             wq[v] = acc;
           }
           Prim1 pr;
           ok = prim1(a.ph, wq, pr) && ok;
           double f[V];
           flux1(wq, pr, f);
-          const double rate = a.ph.k_pre * wq[3] * exp(-a.ph.e_act * (pr.rho / pr.p));
+          // (the exponent held to where exp is 0 or infinite in FP64)
+          const double rate = a.ph.k_pre * wq[3] * exp_taylor(fmin(fmax(-a.ph.e_act * (pr.rho * recip(pr.p)), -800.0), 800.0));
 #pragma unroll
           for (int j = 0; j < M; ++j) {
-            const double g = a.tb.WG[q][j];
+            if (j > 0) {   // P_0' = 0
+              const double g = a.tb.WG[q][j];
 #pragma unroll
-            for (int v = 0; v < V; ++v) vol[v][j] += g * f[v];
-            srcR[j] += a.tb.WB[q][j] * (-rate);
+              for (int v = 0; v < V; ++v) vol[v][j] += g * f[v];
+            }
+            srcR[j] -= a.tb.WB[q][j] * rate;
           }
         }
         double wr_[V][M];
@@ -624,22 +629,23 @@ __device__ __forceinline__ void euler_step_body(const EulerArgs &a, const Limite
           load_elem<M>(win, E, xr, wk);
         }
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
+        for (int j = 0; j < M; ++j) {
+          const double cb_j = a.dt_dx * (2 * j + 1), src = a.dt_2 * (2 * j + 1) * srcR[j];
 #pragma unroll
-          for (int j = 0; j < M; ++j) {
-            const double half2j1 = 0.5 * (2 * j + 1);
-            double sr = 0.0;
-            if (v == 3) sr = srcR[j];
-            if (v == 4) sr = -srcR[j];
-            const double L = a.two_over_dx * (half2j1 * vol[v][j]) + half2j1 * sr;
-            // explicit fused multiply-adds: every kernel that runs this combination rounds alike
+          for (int v = 0; v < V; ++v) {
+            // explicit fused multiply-adds: every kernel that runs this combination rounds alike.  In
+            // the first stage ca is 0 (and cb 1, or the 2N register 0)
             if constexpr (RK == 0) {
-              const double y = fma(a.dt, L, u[v][j]);
-              u[v][j] = use_prev ? fma(ca, wk[v][j], cb * y) : y;
+              double y = fma(cb_j, vol[v][j], u[v][j]);
+              if (v == 3) y += src;
+              if (v == 4) y -= src;
+              u[v][j] = fma(ca, wk[v][j], cb * y);
             } else {
-              const double kn = use_prev ? fma(ca, wn[v][j], a.dt * L) : a.dt * L;
-              wn[v][j] = kn;
-              u[v][j] = fma(cb, kn, u[v][j]);
+              double dl = cb_j * vol[v][j];
+              if (v == 3) dl += src;
+              if (v == 4) dl -= src;
+              wn[v][j] = fma(ca, wn[v][j], dl);
+              u[v][j] = fma(cb, wn[v][j], u[v][j]);
             }
             if constexpr (LIM) ls[(v * M + j) * 64 + lane] = u[v][j];
           }
@@ -724,11 +730,15 @@ __device__ __forceinline__ void euler_step_body(const EulerArgs &a, const Limite
 // then packs a CU in steps of one wavefront.
 template <bool LIM>
 constexpr int kEulerWaves = LIM ? 1 : 4;
+// Wavefronts per SIMD that the registers are held to.  Without a bound N_p = 4 takes 262 registers, one
+// wavefront: 216 us per step at E = 2^20, 158 with two (15.6 and 16.0 at E = 4000, where there is one).
+template <int M, bool LIM>
+constexpr int kEulerMinWaves = LIM ? (M <= 3 ? 3 : 2) : M == 5 ? 2 : 1;
 template <int M, int S, bool LIM>
 constexpr int euler_wave_lds() { return LIM ? lds_wave_doubles<M, S>() : fat_wave_doubles<S>(); }
 
 template <int M, int FLUX, int S>
-__global__ __launch_bounds__(64 * kEulerWaves<false>) void euler_step_kernel(EulerArgs a) {
+__global__ __launch_bounds__(64 * kEulerWaves<false>, (kEulerMinWaves<M, false>)) void euler_step_kernel(EulerArgs a) {
   __shared__ double lds[kEulerWaves<false> * euler_wave_lds<M, S, false>()];
   const int w = threadIdx.x >> 6;
   euler_step_body<M, FLUX, S, false>(a, LimiterArgs{}, a.ws, a.wout, lds + w * euler_wave_lds<M, S, false>(),
@@ -736,7 +746,7 @@ __global__ __launch_bounds__(64 * kEulerWaves<false>) void euler_step_kernel(Eul
 }
 
 template <int M, int FLUX, int S>
-__global__ __launch_bounds__(64 * kEulerWaves<true>, M <= 3 ? 3 : 2) void euler_lim_step_kernel(EulerArgs a, LimiterArgs l) {
+__global__ __launch_bounds__(64 * kEulerWaves<true>, (kEulerMinWaves<M, true>)) void euler_lim_step_kernel(EulerArgs a, LimiterArgs l) {
   __shared__ double lds[kEulerWaves<true> * euler_wave_lds<M, S, true>()];
   const int w = threadIdx.x >> 6;
   euler_step_body<M, FLUX, S, true>(a, l, a.ws, a.wout, lds + w * euler_wave_lds<M, S, true>(),
@@ -748,7 +758,7 @@ __global__ __launch_bounds__(64 * kEulerWaves<true>, M <= 3 ? 3 : 2) void euler_
 // reached its target is skipped by all of its workgroups alike (its first one carries the count over
 // to the other parity).  w^n of a step lives in W[n mod 2].  Batches run SSP-RK3.
 template <int M, int FLUX, bool LIM>
-__global__ __launch_bounds__(64 * kEulerWaves<LIM>, LIM ? (M <= 3 ? 3 : 2) : 1) void euler_batch_kernel(
+__global__ __launch_bounds__(64 * kEulerWaves<LIM>, (kEulerMinWaves<M, LIM>)) void euler_batch_kernel(
     const EulerSet *__restrict__ sets, const int2 *__restrict__ tiles, int par) {
   __shared__ double lds[kEulerWaves<LIM> * euler_wave_lds<M, 3, LIM>()];
   const int2 tl = tiles[blockIdx.x];

@@ -132,8 +132,7 @@ struct EulerArgs {
   int periodic;
   double *W[2];
   int store_U;          // publish boundary-element outputs for the limiter
-  double dt;
-  double two_over_dx;
+  double dt_dx, dt_2;   // dt/dx and dt/2: the factors of (2j+1) b_j and (2j+1) s_j in dt L_j
   OneStep ph;
   DelayParams dl;
   RingParams ring;

@@ -23,46 +23,12 @@
 
 namespace adg {
 
-// ln 2 to 42 bits (its product with an exponent is exact) and the rest.
-constexpr double kLn2Hi = 0x1.62e42fefa3800p-1, kLn2Lo = 0x1.ef35793c76730p-45, kInvLn2 = 1.4426950408889634;
-
-// exp(x): k = rint(x / ln 2), r = x - k ln 2 in two parts, the Taylor polynomial of degree 13 in
-// |r| <= ln(2)/2 (its remainder is below 2^-57 of the result), 2^k by ldexp, which saturates to 0
-// and infinity.  For finite arguments.
-__device__ __forceinline__ double exp_taylor(double x) {
-  const double k = __builtin_rint(x * kInvLn2);
-  double r = fma(k, -kLn2Hi, x);
-  r = fma(k, -kLn2Lo, r);
-  double p = 1.0 / 6227020800.0;
-  p = fma(p, r, 1.0 / 479001600.0);
-  p = fma(p, r, 1.0 / 39916800.0);
-  p = fma(p, r, 1.0 / 3628800.0);
-  p = fma(p, r, 1.0 / 362880.0);
-  p = fma(p, r, 1.0 / 40320.0);
-  p = fma(p, r, 1.0 / 5040.0);
-  p = fma(p, r, 1.0 / 720.0);
-  p = fma(p, r, 1.0 / 120.0);
-  p = fma(p, r, 1.0 / 24.0);
-  p = fma(p, r, 1.0 / 6.0);
-  p = fma(p, r, 0.5);
-  p = fma(p, r, 1.0);
-  p = fma(p, r, 1.0);
-  return __builtin_amdgcn_ldexp(p, (int)k);
-}
-
 // Forms the values here: left to itself the compiler moves the arithmetic past the barriers to its
 // uses and keeps all of its operands (four times the registers) alive until then.
 template <int N>
 __device__ __forceinline__ void pin(double (&x)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
-}
-
-// 1/x by the hardware estimate and two Newton steps, for x away from the ends of the range.
-__device__ __forceinline__ double recip(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return fma(fma(-x, y, 1.0), y, y);
 }
 
 // exp_taylor of N arguments, their dependent chains side by side.

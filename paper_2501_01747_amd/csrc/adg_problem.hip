@@ -311,8 +311,8 @@ adg_status setup_problem(const adg_physics *phys, const adg_discretization *disc
     a.periodic = periodic;
     a.store_U = disc->limiter && L.nif > 0;
     for (int b = 0; b < 2; ++b) a.W[b] = P.W[b];
-    a.dt = disc->dt;
-    a.two_over_dx = 2.0 / dx;
+    a.dt_dx = disc->dt / dx;
+    a.dt_2 = 0.5 * disc->dt;
     a.ph = {phys->gamma, phys->q_heat, phys->e_act, phys->k_pre};
     a.dl = dl;
     a.ring = rp;

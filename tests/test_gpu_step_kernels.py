@@ -68,3 +68,20 @@ def test_whole_step_limiter_tiles(adg, orc, rk, E, bc):
     stages = {"ssprk3": 3, "rk2": 2, "lserk4": 5}[rk]
     assert flags.all() and total == 10 * stages * E
     s.close()
+
+
+@pytest.mark.parametrize("limiter", [0, 1])
+@pytest.mark.parametrize("e_act", [0.0, 3.0, 700.0, 1e7, 1e300])
+def test_reaction_exponents(adg, orc, e_act, limiter):
+    """Arrhenius exponents from 0 to where the rate underflows, and far beyond the bound that the kernel
+    holds them to."""
+    case, w0 = gen.case_c0(E=130, order_p=2, n_pe=4, cfl=0.05, k_pre=1e2)
+    case["physics"]["e_act"] = e_act
+    case["disc"].update(limiter=limiter, indicator="all", flux="hllc")
+    s = adg.Solver(case)
+    s.set_state(w0)
+    o = orc.OracleSolver(case, w0, 13)
+    s.step(12)
+    o.step(12)
+    check(s.state(), o.state(), case, 1e-10, f"e_act={e_act}")
+    s.close()
