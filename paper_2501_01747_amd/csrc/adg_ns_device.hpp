@@ -19,15 +19,23 @@ __device__ __forceinline__ bool newton_T(const double (&c)[6], double T0, double
   T = T0;
   bool conv = false;
   for (int it = 0; it < 50; ++it) {
-    const double e = T * (c[0] + T * (c[1] + T * (c[2] + T * (c[3] + T * c[4])))) + c[5];
-    const double cvi = c[0] + T * (d1 + T * (d2 + T * (d3 + T * d4)));
+    const double T2 = T * T;   // by powers of T^2: the shorter dependent chain
+    const double e = fma(T2, fma(T2, fma(T, c[4], c[3]), fma(T, c[2], c[1])), fma(T, c[0], c[5]));
+    const double cvi = fma(T2, fma(T2, d4, fma(T, d3, d2)), fma(T, d1, c[0]));
     const double dT = (e - estar) * __builtin_amdgcn_rcp(cvi);   // the correction needs no IEEE quotient
     T -= dT;
     if (!(T > 0.0) || !isfinite(T)) break;
     if (fabs(dT) <= 1e-8 * T) { conv = true; break; }
   }
-  cv = c[0] + T * (d1 + T * (d2 + T * (d3 + T * d4)));
+  const double T2 = T * T;
+  cv = fma(T2, fma(T2, d4, fma(T, d3, d2)), fma(T, d1, c[0]));
   return conv;
+}
+
+// x within [0, E) by whole periods; x lies in [-span, E + span).
+__device__ __forceinline__ int wrap(int x, int E, int span) {
+  if (E < span) return (x % E + E) % E;   // meshes shorter than a tile
+  return x < 0 ? x + E : x >= E ? x - E : x;
 }
 
 // AT combination (Eq. (7)) of the central trace and the flux of variable v at interface i from

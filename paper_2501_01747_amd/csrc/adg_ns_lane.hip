@@ -93,12 +93,6 @@ struct LaneLds {
   };
 };
 
-// x within [0, E) by whole periods; x lies in [-span, E + span).
-__device__ __forceinline__ int wrap(int x, int E, int span) {
-  if (E < span) return (x % E + E) % E;   // meshes shorter than a tile
-  return x < 0 ? x + E : x >= E ? x - E : x;
-}
-
 // The tile's faces: interface index (or -1), effective delay, and the number of interfaces.
 template <int NF>
 struct LanePe {
