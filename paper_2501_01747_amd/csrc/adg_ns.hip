@@ -629,7 +629,9 @@ __device__ __forceinline__ void ns_tile(const NsArgs &a, const double *__restric
   }
   __syncthreads();
   {
-    constexpr int kSlots = NP <= 32 ? 32 : 64;   // point slots per workgroup
+    // point slots per workgroup (8 lanes a point with 512 threads, whatever the tile: the sums over a
+    // group then round alike, and 4/512 gives what 8/512 gives bit for bit)
+    constexpr int kSlots = NP <= 32 && NTH < 512 ? 32 : 64;
     constexpr int LP = NTH / kSlots;   // lanes per point
     static_assert(LP >= 1 && LP <= 64 && (LP & (LP - 1)) == 0 && NP <= NTH / LP, "every point has a lane group");
     constexpr int NO = (NS + LP - 1) / LP;
@@ -1042,10 +1044,12 @@ static int tiles_per_cu(int M) {
 // Measured (us per stage, one box, N_p = 3, 9 species; 8/512, 8/256, a lane per point):
 //   E = 2048   9.8 11.1 18.2     E = 4096   12.3 12.9 18.5     E = 6144  18.8 14.9 18.6
 //   E = 8192  21.6 16.3 20.0     E = 12288  31.3 24.9 20.5     E = 2^15  77.2 53.1 30.5
-// and the same lines for N_p = 1, 2, 4.  While all tiles of 8 are resident at once the spread kernels
-// win: their latency per tile is about half of a lane's that forms every species and reaction of its
-// point; 512 threads while two tiles a CU hold the problem (256 CUs), 256 threads while the LDS holds
-// it.  Beyond, the lane-per-point kernel's fewer instructions do, with 16 species from 12288 elements
+// and the same lines for N_p = 1, 2, 4.  While a CU has no more than one tile of 4, that tile is the
+// shortest chain: 8/512 and 4/512 take 9.2 and 8.7 at E = 16, 9.3 and 8.9 at E = 1024 (N_p = 4: 9.9 and
+// 9.2 at 150; 16 species, N_p = 4: 11.8 and 10.0 at 1024), but 9.5 and 10.0 at E = 1400.
+// While all tiles of 8 are resident at once the spread kernels win: their latency per tile is about half
+// of a lane's that forms every species and reaction of its point; 512 threads while two tiles a CU
+// hold the problem (256 CUs), 256 threads while the LDS holds it.  Beyond, the lane-per-point kernel's fewer instructions do, with 16 species from 12288 elements
 // on (a lane's chain is longer: 16384 elements at N_p = 3 take 46.6, 53.0 and 34.4, 8192 take 25.2,
 // 27.8 and 29.7).
 int ns_kernel_of(int cfg, int E, int M, int ns) {
@@ -1056,6 +1060,7 @@ int ns_kernel_of(int cfg, int E, int M, int ns) {
   if (cfg == 1) return lane ? kNsLane : 1;
   if (cfg == 0) return 0;
   if (lane) return kNsLane;
+  if ((E + 3) / 4 <= kCus) return 3;
   const int tiles = (E + 7) / 8;
   const int fit = wide ? tiles_per_cu<kNsWideSpecies>(M) : tiles_per_cu<kNsMaxSpecies>(M);
   return tiles > 2 * kCus && tiles <= fit * kCus ? 1 : 0;

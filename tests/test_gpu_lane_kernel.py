@@ -100,3 +100,24 @@ def test_single_problems(adg, orc, ns, E, rk):
     assert float(np.max(var_errors(s.state(), o.state()))) < 1e-10
     check(s.state(), o.state(), case, 1e-10, "single")
     s.close()
+
+
+@pytest.mark.parametrize("E,species", [(1, 9), (1023, 9), (1024, 9), (1025, 9), (1024, 16), (1025, 16)])
+def test_untuned_choice_of_small_meshes(adg, orc, mech, E, species):
+    """Either side of the last mesh that gives each of 256 CUs one tile of 4 elements: against the oracle,
+    and bit for bit what the tile of 8 with 512 threads gives."""
+    c, w = gen.case_c1(E=E, order_p=2, n_pe=min(E, 7), mech=mech if species == 9 else mechanism_of(species), cfl=0.08,
+                       Lx=0.01 * max(E, 8) / 2048)
+    got = []
+    for config in (None, 0):
+        s = adg.Solver(c)
+        if config is not None:
+            s.set_kernel_config(config)
+        s.set_state(w)
+        s.step(5)
+        got.append(s.state())
+        s.close()
+    o = orc.OracleSolver(c, w, 6)
+    o.step(5)
+    check(got[0], o.state(), c, 1e-10, f"E={E} species={species}")
+    assert np.array_equal(got[0], got[1])
