@@ -31,6 +31,7 @@
 // 16.1 against 16.8 at E = 5001, N_p = 2, 16 species.
 #include "adg_ns_device.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <type_traits>
@@ -936,6 +937,7 @@ adg_status ns_build_mech(const adg_physics *ph, NsMechT<NSC> &hm) {
     hm.ek[i][6] = hm.Ri[i];
     hm.ek[i][7] = 0.0;
   }
+  hm.invT_factored = 1e300;
   for (int r = 0; r < hm.nr; ++r) {
     if (!(m->A[r] > 0.0)) return ADG_ERR_ARG;
     hm.lnA[r] = std::log(m->A[r]);
@@ -972,9 +974,17 @@ adg_status ns_build_mech(const adg_physics *ph, NsMechT<NSC> &hm) {
       }
     }
     auto &x = hm.rx[r];
-    x.lnA = hm.lnA[r];
-    x.b = hm.b[r];
-    x.EaR = hm.EaR[r];
+    if (hm.EaR[r] > kNsNoRate) {
+      x.lnA = -1e8;   // rate zero; the exponent stays in the range of the lane kernels' exponential
+    } else {
+      x.lnA = hm.lnA[r];
+      x.b = hm.b[r];
+      x.EaR = hm.EaR[r];
+      // the least of ln A + b ln T over 50 .. 20000 K
+      const double least = x.lnA + std::min(x.b * 3.9, x.b * 9.9);
+      if (x.EaR > 0.0) hm.invT_factored = std::min(hm.invT_factored, (kNsMaxLnRate + least) / x.EaR);
+      else if (least < -kNsMaxLnRate) hm.invT_factored = -1.0;
+    }
     for (int c = 0; c < 2; ++c) {
       x.sp[c] = (unsigned short)(hm.rf[r][c] < 0 ? NSC : hm.rf[r][c]);
       x.sp[2 + c] = (unsigned short)(hm.rr[r][c] < 0 ? NSC : hm.rr[r][c]);

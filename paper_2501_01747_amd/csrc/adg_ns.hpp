@@ -14,6 +14,10 @@ constexpr int kNsWideSpecies = 16;    // single problems with 9 < Ns <= 16
 constexpr int kNsMaxReactions = 32;
 constexpr int kNsReactionGroup = 2;   // reactions that a lane of the lane-per-point kernels forms side by side
 constexpr int kNsBatchReactions = 24;   // reactions of a batched mechanism
+// Ea/Ru (K) from which a reaction has no rate in either direction at any temperature of the thermo
+// (exp underflows by 2000 and more at 5e5 K), and the size of ln k_f up to which the lane-per-point
+// kernels form a reverse rate from k_f.
+constexpr double kNsNoRate = 1e9, kNsMaxLnRate = 650.0;
 inline int ns_capacity(int n_species) { return n_species <= kNsMaxSpecies ? kNsMaxSpecies : kNsWideSpecies; }
 
 // Mechanism in device memory, read with wave-uniform indices (scalar loads), for kernels of
@@ -59,6 +63,9 @@ struct NsMechCoreT {
 // in the order they are read, each a whole number of 64-byte scalar loads.
 template <int NSC>
 struct NsMechT : NsMechCoreT<NSC> {
+  // Largest 1/T at which no forward rate constant is near the end of the range of exp: there the
+  // rates may be formed from it and the species' factors, whose product would be lost with it.
+  double invT_factored;
   struct alignas(64) Species {
     double a0, h2[4], a5;          // h_i/R_i = T (a0 + T (h2[0] + ...)) + a5
     double a1, s2[3], a6;          // s_i/R_i = a0 ln T + T (a1 + T (s2[0] + ...)) + a6

@@ -31,7 +31,7 @@ __device__ __forceinline__ void pin(double (&x)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
 }
 
-// exp_taylor of N arguments, their dependent chains side by side.
+// exp_taylor of N arguments (of a size below 2^31), their dependent chains side by side.
 template <int N>
 __device__ __forceinline__ void exp_taylor_n(double (&x)[N]) {
   double k[N], r[N], p[N];
@@ -393,7 +393,8 @@ __device__ __forceinline__ void ns_lane_tile(const NsArgs &a, const double *__re
     D[0] = X[1];
     D[1] = g1;
     D[2] = g2;
-    fast = __all(!(node && valid) || big == 0.0);
+    // (a forward constant that underflows takes a reverse rate formed from it along, though that may be large)
+    fast = __all(!(node && valid) || (big == 0.0 && invT <= mk->invT_factored));
     if (t >= (T0 & ~63)) {
       // Rusanov total flux f = (g- + g+)/2 - lambda (w+ - w-)/2, formed by the right lane of a
       // face's pair from its neighbour's values; at PE interfaces the synchronous flux is published

@@ -121,3 +121,51 @@ def test_untuned_choice_of_small_meshes(adg, orc, mech, E, species):
     o.step(5)
     check(got[0], o.state(), c, 1e-10, f"E={E} species={species}")
     assert np.array_equal(got[0], got[1])
+
+
+def test_rates_at_the_ends_of_the_range_of_exp(adg, orc, mech):
+    """Channels switched off by an activation energy of any size (the largest exponents a double holds, and
+    some where only the forward rate is zero), in a batch and in a single problem of the size that takes
+    this kernel, against the oracle."""
+    Ea = mech["Ea"].copy()
+    Ea[[0, 3, 7, 20]] = 1e300, 1e12, 3e8, 8e6
+    off = dict(mech, Ea=Ea)
+    run_batch(adg, orc, [gen.case_c1(E=E, n_pe=4, mech=off, Lx=0.01 * E / 2048) for E in (5, 70)], 10)
+    case, w0 = gen.case_c1(E=8200, n_pe=4, mech=off, Lx=0.01 * 8200 / 2048)
+    s = adg.Solver(case)
+    s.set_state(w0)
+    s.step(3)
+    o = orc.OracleSolver(case, w0, 4)
+    o.step(3)
+    check(s.state(), o.state(), case, 1e-10, "single")
+    s.close()
+
+
+def test_reverse_rate_of_a_forward_rate_of_zero(adg, mech):
+    """A reaction 2 X = 2 Y whose forward rate constant underflows at every temperature of the mesh but whose
+    reverse one is e^26, Y lying 3.9 MJ/mol above X and the species' factors of the equilibrium constant
+    within exp(250): the batched kernel against the single problem's, which forms the two constants apart.
+    Bound: that of the other parity tests, 1e-10; without the reverse rate Y stays as it was."""
+    ix, iy = mech["names"].index("A"), mech["names"].index("B")
+    nasa, W = mech["nasa7"].copy(), mech["W"].copy()
+    W[ix] = W[iy]
+    nasa[ix] = (3.0, 1e-3, 0.0, 0.0, 0.0, -232e3, -20.0)
+    nasa[iy] = (3.0, 1e-3, 0.0, 0.0, 0.0, 232e3, -20.0)
+    nu_f, nu_r = (np.zeros((1, mech["n_species"]), np.int32) for _ in range(2))
+    nu_f[0, ix] = nu_r[0, iy] = 2
+    one = dict(mech, nasa7=nasa, W=W, n_reactions=1, nu_f=nu_f, nu_r=nu_r, A=np.array([np.exp(26.0)]),
+               b=np.zeros(1), Ea=np.array([928e3 * gen.RU]))
+    case, w0 = gen.case_c1(E=40, n_pe=2, mech=one, Lx=0.01 * 40 / 2048)
+    s = adg.Solver(case)
+    s.set_state(w0)
+    s.step(10)
+    b = adg.Batch(1, 40, adg.Batch.instance_bytes(case))
+    sl = b.add(case, w0)
+    b.step(10)
+    got, ref = b.state(sl), s.state()
+    b.close()
+    s.close()
+    y = ref[:, 3 + iy, 0] / w0[:, 3 + iy, 0]
+    print("[lane] Y / Y(0):", y.min(), y.max(), flush=True)
+    assert y.max() < 0.99
+    check(got, ref, case, 1e-10, "reverse rate")
