@@ -42,6 +42,7 @@ struct adg_solver {
   int graph_par[2] = {0, 0}, graph_par_after[2] = {0, 0};
   int ns_cfg = -1;  // work decomposition of the detailed-chemistry stage kernel (-1: none chosen)
   bool at_ready = false;   // the last launch left its successor's AT combinations (set_at_buffers)
+  bool captured = false;   // the caller has captured calls on this solver into graphs of its own
   int graph_steps = 0;
   int graph_built_for = 0;
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -153,6 +154,18 @@ adg_status enqueue_step(adg_solver *s, hipStream_t st, TimerFn timer) {
   }
   next_alignment(s, s->cur, s->par);
   return ADG_OK;
+}
+
+// Brackets of the calls that launch steps.  A solver that the caller has captured (or is capturing) may
+// have been stepped by replays since the last call: the state goes to the buffer that the host steps from
+// and back, and the first launch relies on no carried AT values.
+hipError_t align(adg_solver *s, bool begin) {
+  if (begin && capturing(s->stream)) s->captured = true;
+  if (!s->captured) return hipSuccess;
+  s->at_ready = false;
+  int cur = 0, par = 0;
+  next_alignment(s, cur, par);
+  return launch_align(s->P, cur != 0, s->cur, begin, s->stream);
 }
 
 void destroy_graph(adg_solver *s) {
@@ -286,11 +299,11 @@ adg_status adg_set_state(adg_solver *s, const double *w, int64_t count, int32_t 
   s->par = 0;
   s->at_ready = false;
   s->graph_replays = 0;
+  if (capturing(s->stream)) s->captured = true;
   return ADG_OK;
 }
 
-adg_status adg_step(adg_solver *s, int32_t n_steps) {
-  if (!s || n_steps < 0) return ADG_ERR_ARG;
+static adg_status run_steps(adg_solver *s, int n_steps) {
   if (s->graph_steps > 0) {
     if (s->graph_built_for != s->graph_steps) {
       adg_status rc = build_graph(s);
@@ -324,6 +337,14 @@ adg_status adg_step(adg_solver *s, int32_t n_steps) {
   return ADG_OK;
 }
 
+adg_status adg_step(adg_solver *s, int32_t n_steps) {
+  if (!s || n_steps < 0) return ADG_ERR_ARG;
+  HIP_TRY(s, align(s, true));
+  adg_status rc = run_steps(s, n_steps);
+  if (rc == ADG_OK) HIP_TRY(s, align(s, false));
+  return rc;
+}
+
 static adg_status state_status(adg_solver *s, int err) {
   if (err) return fail(s, ADG_ERR_STATE, "non-physical state (rho <= 0, p <= 0, non-finite or no T convergence)");
   return ADG_OK;
@@ -350,6 +371,7 @@ adg_status adg_get_state(adg_solver *s, double *w, int64_t count, int32_t where)
     s->host_err = nullptr;
   }
   s->reads = std::min(s->reads + 1, 2);
+  HIP_TRY(s, align(s, true));
   if (where == ADG_HOST) {
     HIP_TRY(s, get_state_host(s->P, s->P.W[s->cur], w, s->host_err, s->stream));
   } else if (where == ADG_DEVICE) {
@@ -396,10 +418,12 @@ static void prof_timer(adg_solver *s, int cls, bool begin) {
 adg_status adg_profile(adg_solver *s, int32_t n_steps, double *ms_out, int64_t *launches_out, int32_t n_classes) {
   if (!s || n_steps < 1 || !ms_out || !launches_out || n_classes < 1) return ADG_ERR_ARG;
   s->prof_events.clear();
+  HIP_TRY(s, align(s, true));
   for (int i = 0; i < n_steps; ++i) {
     adg_status rc = enqueue_step(s, s->stream, prof_timer);
     if (rc != ADG_OK) return rc;
   }
+  HIP_TRY(s, align(s, false));
   // the launches of one step, all of class 0
   const std::vector<int> order(s->prof_events.size() / 2 / n_steps, 0);
   HIP_TRY(s, hipStreamSynchronize(s->stream));
@@ -428,6 +452,7 @@ adg_status adg_autotune(adg_solver *s, int32_t n_reps, int32_t *choice) {
   if (choice) *choice = 0;
   if (s->P.phys.model != ADG_DETAILED) return ADG_OK;   // one decomposition only
   const int M = s->P.lay.M;
+  HIP_TRY(s, align(s, true));
   // first-stage launches only: they read the state and write the first stage's output
   // buffer (and the 2N register, whose old value the first stage does not read) and the
   // level's first-stage history, all of which the next step recomputes; the state is untouched
@@ -470,6 +495,7 @@ adg_status adg_autotune(adg_solver *s, int32_t n_reps, int32_t *choice) {
   if (t[best] > 0.97 * t[0]) best = 0;
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
+  HIP_TRY(s, align(s, false));
   if (best != s->ns_cfg) {
     s->ns_cfg = best;
     destroy_graph(s);

@@ -401,6 +401,46 @@ hipError_t launch_copies(const Copies &c, hipStream_t st) {
   return hipGetLastError();
 }
 
+__device__ __forceinline__ long long level_counts(long long *c, bool store) {
+  const long long n = max(c[0], c[1]);
+  if (store) c[0] = c[1] = n;   // (the same maximum for whoever reads them meanwhile)
+  return n;
+}
+
+__global__ __launch_bounds__(kPlaneThreads) void level_counts_kernel(long long *counters, int n) {
+  const int i = blockIdx.x * kPlaneThreads + threadIdx.x;
+  if (i < n) level_counts(counters + 2 * (size_t)i, true);
+}
+
+hipError_t launch_level_counts(long long *counters, int n, hipStream_t st) {
+  hipLaunchKernelGGL(level_counts_kernel, dim3((n + kPlaneThreads - 1) / kPlaneThreads), dim3(kPlaneThreads), 0, st, counters, n);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(kPlaneThreads) void align_kernel(long long *counters, double *w0, double *w1, size_t doubles,
+                                                              int cur, bool begin) {
+  const int at = (int)(level_counts(counters, blockIdx.x == 0 && threadIdx.x == 0) & 1);
+  if (at == cur) return;
+  const double *src = (begin ? at : cur) ? w1 : w0;
+  double *dst = (begin ? cur : at) ? w1 : w0;
+  for (size_t i = (size_t)blockIdx.x * kPlaneThreads + threadIdx.x; i < doubles; i += (size_t)gridDim.x * kPlaneThreads)
+    dst[i] = src[i];
+}
+
+hipError_t launch_align(const Problem &P, bool alternates, int cur, bool begin, hipStream_t st) {
+  if (!alternates) return launch_level_counts(P.step, 1, st);
+  const size_t n = state_doubles(P.lay.E, P.lay.V * P.lay.M);
+  const unsigned blocks = (unsigned)std::min<size_t>(2048, (n + 4 * kPlaneThreads - 1) / (4 * kPlaneThreads));
+  hipLaunchKernelGGL(align_kernel, dim3(blocks), dim3(kPlaneThreads), 0, st, P.step, P.W[0], P.W[1], n, cur, begin);
+  return hipGetLastError();
+}
+
+bool capturing(hipStream_t st) {
+  if (!st) return false;   // the null stream cannot be captured
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &c) == hipSuccess && c == hipStreamCaptureStatusActive;
+}
+
 // A new state: the first `blocks` workgroups change its layout, the others clear what it resets (a
 // kernel, not hipMemsetAsync: a caller may capture it into a HIP graph).
 __global__ __launch_bounds__(kPlaneThreads) void set_state_kernel(const double *__restrict__ src, double *__restrict__ dst,
@@ -421,10 +461,14 @@ __global__ __launch_bounds__(kPlaneThreads) void set_state_kernel(const double *
   }
 }
 
-// The state in the caller's layout, and the error flag beside it (err_out, may be null).
-__global__ __launch_bounds__(kPlaneThreads) void get_state_kernel(const double *__restrict__ src, double *__restrict__ dst,
-                                                                 int E, int VM, const int *err, int *err_out) {
+// The state in the caller's layout, and the error flag beside it (err_out, may be null).  With `count`
+// the state is in src or in src1, by its parity.
+__global__ __launch_bounds__(kPlaneThreads) void get_state_kernel(const double *__restrict__ src,
+                                                                 const double *__restrict__ src1, const long long *count,
+                                                                 double *__restrict__ dst, int E, int VM, const int *err,
+                                                                 int *err_out) {
   extern __shared__ double lds[];
+  if (count && (*count & 1)) src = src1;
   const int blk = blockIdx.x;
   const int ne = min(kLayoutBlock, E - blk * kLayoutBlock), row = VM | 1;
   const double *s = src + (size_t)blk * kLayoutBlock * VM;
@@ -464,20 +508,23 @@ hipError_t set_state_device(const Problem &P, const double *w, hipStream_t st, c
   return hipGetLastError();
 }
 
-hipError_t get_state_device(const Problem &P, const double *buf, double *w, int *err_out, hipStream_t st) {
+hipError_t get_state_device(const Problem &P, const double *buf, double *w, int *err_out, hipStream_t st,
+                            const long long *count) {
   const Layout &L = P.lay;
   const int VM = L.V * L.M, blocks = (L.E + kLayoutBlock - 1) / kLayoutBlock;
-  hipLaunchKernelGGL(get_state_kernel, dim3(blocks), dim3(kPlaneThreads), plane_lds(VM), st, buf, w, L.E, VM, P.err, err_out);
+  hipLaunchKernelGGL(get_state_kernel, dim3(blocks), dim3(kPlaneThreads), plane_lds(VM), st, count ? P.W[0] : buf, P.W[1],
+                     count, w, L.E, VM, P.err, err_out);
   return hipGetLastError();
 }
 
-// Host states change their layout on the device, through a state buffer that is free between steps.
-static double *free_buffer(const Problem &P, const double *state) {
-  return P.phys.model == ADG_ONESTEP ? P.W[2] : state == P.W[1] ? P.W[0] : P.W[1];
+// Host states change their layout on the device, through a buffer that holds no state between steps: the
+// one-step model's third, the 2N register, or SSP-RK3's first stage.
+static double *free_buffer(const Problem &P) {
+  return P.phys.model == ADG_ONESTEP || rk_stage(P.disc.rk, 0).two_n ? P.W[2] : P.W[1];
 }
 
 hipError_t set_state_host(const Problem &P, const double *w, hipStream_t st, const Copies *copies) {
-  double *buf = free_buffer(P, P.W[0]);
+  double *buf = free_buffer(P);
   const size_t bytes = sizeof(double) * (size_t)P.lay.E * P.lay.V * P.lay.M;
   hipError_t e = hipMemcpyAsync(buf, w, bytes, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = set_state_device(P, buf, st, copies);
@@ -485,10 +532,11 @@ hipError_t set_state_host(const Problem &P, const double *w, hipStream_t st, con
   return e == hipSuccess ? done : e;
 }
 
-hipError_t get_state_host(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st) {
-  double *buf = free_buffer(P, state);
+hipError_t get_state_host(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st,
+                          const long long *count) {
+  double *buf = free_buffer(P);
   const size_t bytes = sizeof(double) * (size_t)P.lay.E * P.lay.V * P.lay.M;
-  hipError_t e = get_state_device(P, state, buf, err_out, st);
+  hipError_t e = get_state_device(P, state, buf, err_out, st, count);
   if (e == hipSuccess) e = hipMemcpyAsync(w, buf, bytes, hipMemcpyDeviceToHost, st);
   const hipError_t done = hipStreamSynchronize(st);
   return e == hipSuccess ? done : e;

@@ -67,13 +67,25 @@ struct Copies {
   size_t words[kCopies];
 };
 hipError_t launch_copies(const Copies &c, hipStream_t st);
+// Whether the caller is capturing stream st into a graph of its own.  The host does not see the replays
+// of such a graph, so from the first capture on the calls that step are bracketed by the two below: what
+// the host holds (counter parity, state buffer) then fits whatever ran in between.
+bool capturing(hipStream_t st);
+// Both parities' counters of n problems to the greater one, the steps done.
+hipError_t launch_level_counts(long long *counters, int n, hipStream_t st);
+// The same for one problem, whose state is in buffer W[steps done mod 2] between calls where it alternates
+// (`alternates`): moved to W[cur] (begin) or from W[cur] back there.
+hipError_t launch_align(const Problem &P, bool alternates, int cur, bool begin, hipStream_t st);
 // A new state w ([E][V][M]) in W[0], the step counters, error flag, history ring and flags back to
 // zero, with `copies` in the same launch: enqueued (capturable); the host form copies w first and waits.
 hipError_t set_state_device(const Problem &P, const double *w, hipStream_t st, const Copies *copies = nullptr);
 hipError_t set_state_host(const Problem &P, const double *w, hipStream_t st, const Copies *copies = nullptr);
 // The state in buffer `state` (one of P.W) in the caller's layout, and the error flag in *err_out
-// (device-accessible; null: not reported): enqueued; the host form waits.
-hipError_t get_state_device(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st);
-hipError_t get_state_host(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st);
+// (device-accessible; null: not reported): enqueued; the host form waits.  With `count` (device) the
+// buffer is W[*count mod 2] instead.
+hipError_t get_state_device(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st,
+                            const long long *count = nullptr);
+hipError_t get_state_host(const Problem &P, const double *state, double *w, int *err_out, hipStream_t st,
+                          const long long *count = nullptr);
 
 }  // namespace adg

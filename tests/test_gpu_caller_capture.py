@@ -1,0 +1,94 @@
+"""Steps that the caller captures into a HIP graph of its own and replays, with eager steps, a new state and
+reads between the replays: bit for bit what eager steps give, for even and odd numbers of steps."""
+import numpy as np
+import pytest
+
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def adg():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2501_01747_amd import adg as lib
+
+    return lib
+
+
+def capture(obj, n):
+    import torch
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=obj.stream):
+        obj.step(n)
+    return g
+
+
+def problem(kind):
+    if kind == "detailed" or kind == "detailed lserk4":
+        case, w0 = gen.case_c1(E=70, order_p=2, n_pe=6, cfl=0.08, Lx=0.01 * 70 / 2048)
+    elif kind == "limited":
+        case, w0 = gen.case_shock(160, 2, n_pe=5)
+    else:
+        case, w0 = gen.case_c0(E=130, n_pe=8, pmf=(0.3, 0.4, 0.3), mode="sync" if kind == "sync" else "saa")
+    if kind in ("rk2", "lserk4", "detailed lserk4"):
+        case["disc"]["rk"] = kind.split()[-1]
+    return case, w0
+
+
+@pytest.mark.parametrize("n", [1, 2, 3])
+@pytest.mark.parametrize("kind", ["sync", "saa", "rk2", "lserk4", "limited", "detailed", "detailed lserk4"])
+def test_solver_steps_in_a_graph(adg, kind, n):
+    import torch
+
+    case, w0 = problem(kind)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s, ref = adg.Solver(case), adg.Solver(case)
+        s.set_state(w0)
+        ref.set_state(w0)
+        s.step(5)   # an odd alignment, with carried AT values
+        ref.step(5)
+        g = capture(s, n)
+        done = 5
+        for eager in (0, 2, 1, 0):
+            g.replay()
+            s.step(eager)
+            ref.step(n + eager)
+            done += n + eager
+            assert s.step_count() == ref.step_count() == done
+            np.testing.assert_array_equal(s.state(), ref.state())
+        s.set_state(w0)   # replays from a new state need its alignment to be the captured one
+        s.step(5)
+        ref.set_state(w0)
+        ref.step(5 + 2 * n)
+        g.replay()
+        g.replay()
+        np.testing.assert_array_equal(s.state(), ref.state())
+        s.close()
+        ref.close()
+
+
+def test_captured_steps_that_have_not_run(adg):
+    """A capture alone changes nothing: the next eager step reads no values that its launches would carry."""
+    import torch
+
+    case, w0 = gen.case_c1(E=8200, order_p=1, n_pe=300, cfl=0.1, Lx=0.01 * 8200 / 2048)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s, ref = adg.Solver(case), adg.Solver(case)
+        for x in (s, ref):
+            x.set_state(w0)
+            x.step(6)   # by the lane-per-point kernel, which carries nothing
+            x.set_kernel_config(0)
+        g = capture(s, 2)
+        s.step(3)
+        ref.step(3)
+        np.testing.assert_array_equal(s.state(), ref.state())
+        del g
+        s.close()
+        ref.close()
