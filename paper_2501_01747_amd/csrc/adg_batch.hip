@@ -34,7 +34,6 @@ struct Slot {
   Problem P;
   size_t off = 0, bytes = 0;  // heap region
   long long target = kNoTarget;
-  long long admitted = 0;     // batch steps enqueued before its admission
   int mech = -1;              // shared mechanism slot (detailed chemistry)
 };
 
@@ -78,7 +77,7 @@ struct adg_batch {
   long long *d_step = nullptr;   // [slot][2]: each instance's step counters of the two parities
   int *d_err = nullptr;
   int par = 0;                   // step counter parity of the next batch step
-  long long steps = 0;           // batch steps enqueued so far
+  bool captured = false;         // the caller has captured steps of this batch into graphs of its own
   size_t heap_off = 0;
   std::map<size_t, size_t> free_list;  // offset -> bytes
   std::vector<Slot> slots;
@@ -272,7 +271,6 @@ adg_status enqueue_batch_steps(adg_batch *b, hipStream_t st, int steps, bool tim
       }
     }
     b->par ^= 1;   // the step's last launches wrote the next counts into the other counters
-    b->steps += 1;
   }
   if (nstreams > 1) {
     for (int k = 1; k < nstreams; ++k) {
@@ -336,14 +334,12 @@ adg_status build_batch_graph(adg_batch *b) {
   destroy_batch_graph(b);
   if (!b->cap_stream) BHIP(b, hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
   const int par_keep = b->par;
-  const long long steps_keep = b->steps;
   for (int p = 0; p < 2; ++p) {
     b->par = p;
     BHIP(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
     adg_status rc = ADG_OK;
     rc = enqueue_batch_steps(b, b->cap_stream, b->graph_steps, false);
     b->par = par_keep;   // nothing ran: capture only records
-    b->steps = steps_keep;
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(b->cap_stream, &g);
     if (rc != ADG_OK) {
@@ -458,7 +454,6 @@ adg_status adg_batch_add(adg_batch *b, const adg_physics *phys, const adg_discre
   s.off = off;
   s.bytes = need;
   s.target = n_steps > 0 ? n_steps : kNoTarget;
-  s.admitted = b->steps;
   // counters of the slot live in the header so that one copy reads them all
   Problem &P = s.P;
   P.step = b->d_step + 2 * (size_t)slot;
@@ -532,26 +527,33 @@ adg_status adg_batch_remove(adg_batch *b, int32_t slot) {
   return ADG_OK;
 }
 
-adg_status adg_batch_step(adg_batch *b, int32_t n_steps) {
-  if (!b || n_steps < 0) return ADG_ERR_ARG;
-  adg_status rc = prepare(b);
-  if (rc != ADG_OK) return rc;
-  if (b->groups.empty()) return ADG_OK;
+static adg_status run_batch_steps(adg_batch *b, int n_steps) {
   int done = 0;
   if (b->graph_steps > 0) {
     if (!b->graph_valid) {
-      rc = build_batch_graph(b);
+      adg_status rc = build_batch_graph(b);
       if (rc != ADG_OK) return rc;
     }
     // whole graphs from the graph of the current parity, then plain steps for the rest
     while (done + b->graph_steps <= n_steps) {
       BHIP(b, hipGraphLaunch(b->gexec[b->par], b->stream));
       b->par ^= b->graph_steps & 1;
-      b->steps += b->graph_steps;
       done += b->graph_steps;
     }
   }
   return enqueue_batch_steps(b, b->stream, n_steps - done, false);
+}
+
+adg_status adg_batch_step(adg_batch *b, int32_t n_steps) {
+  if (!b || n_steps < 0) return ADG_ERR_ARG;
+  adg_status rc = prepare(b);
+  if (rc != ADG_OK) return rc;
+  if (b->groups.empty()) return ADG_OK;
+  if (capturing(b->stream)) b->captured = true;
+  if (b->captured) BHIP(b, launch_level_counts(b->d_step, b->max_inst, b->stream));
+  rc = run_batch_steps(b, n_steps);
+  if (rc == ADG_OK && b->captured) BHIP(b, launch_level_counts(b->d_step, b->max_inst, b->stream));
+  return rc;
 }
 
 adg_status adg_batch_poll(adg_batch *b, int64_t *steps, int32_t *state_err) {
@@ -579,15 +581,15 @@ adg_status adg_batch_get_state(adg_batch *b, int32_t slot, double *w, int64_t co
   const Problem &P = b->slots[slot].P;
   const Layout &L = P.lay;
   if (count != (int64_t)L.E * L.V * L.M) return bfail(b, ADG_ERR_ARG, "state size mismatch");
-  // one-step instances: the state lives in buffer (step count) mod 2
-  const Slot &sl = b->slots[slot];
-  const double *src = P.phys.model == ADG_ONESTEP ? P.W[std::min(b->steps - sl.admitted, sl.target) & 1] : P.W[0];
+  // one-step instances: the state lives in buffer (step count) mod 2, and the device has the count (the
+  // host does not see the replays of a graph that the caller captured)
+  const long long *steps_done = P.phys.model == ADG_ONESTEP ? P.step + b->par : nullptr;
   char *p = nullptr;
   if (adg_status rc = staging(b, sizeof(int), &p); rc != ADG_OK) return rc;
   if (where == ADG_HOST) {
-    BHIP(b, get_state_host(P, src, w, (int *)p, b->stream));
+    BHIP(b, get_state_host(P, P.W[0], w, (int *)p, b->stream, steps_done));
   } else if (where == ADG_DEVICE) {
-    BHIP(b, get_state_device(P, src, w, (int *)p, b->stream));
+    BHIP(b, get_state_device(P, P.W[0], w, (int *)p, b->stream, steps_done));
     BHIP(b, hipStreamSynchronize(b->stream));
   } else {
     return bfail(b, ADG_ERR_ARG, "where must be ADG_HOST or ADG_DEVICE");
@@ -610,7 +612,9 @@ adg_status adg_batch_profile(adg_batch *b, int32_t n_steps, double *ms_out, int6
   if (rc != ADG_OK) return rc;
   b->prof_events.clear();
   b->prof_class.clear();
+  if (b->captured) BHIP(b, launch_level_counts(b->d_step, b->max_inst, b->stream));
   rc = enqueue_batch_steps(b, b->stream, n_steps, true);
+  if (rc == ADG_OK && b->captured) BHIP(b, launch_level_counts(b->d_step, b->max_inst, b->stream));
   hipError_t he = hipStreamSynchronize(b->stream);
   std::vector<double> sum(n_classes, 0.0);
   std::vector<int64_t> cnt(n_classes, 0);

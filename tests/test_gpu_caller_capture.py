@@ -92,3 +92,29 @@ def test_captured_steps_that_have_not_run(adg):
         del g
         s.close()
         ref.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3])
+def test_batch_steps_in_a_graph(adg, n):
+    import torch
+
+    cases = [gen.case_c0(E=90, n_pe=5, pmf=(0.3, 0.4, 0.3)), gen.case_shock(160, 2, n_pe=5),
+             gen.case_c1(E=40, order_p=2, n_pe=4, cfl=0.08, Lx=0.01 * 40 / 2048), gen.case_c0(E=64, order_p=3, n_pe=3, cfl=0.04)]
+    targets = [0, 0, 0, 7]
+    heap = sum(adg.Batch.instance_bytes(c) for c, _ in cases)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        b, ref = (adg.Batch(4, 400, heap) for _ in range(2))
+        slots = [[x.add(c, w, t) for (c, w), t in zip(cases, targets)] for x in (b, ref)]
+        b.step(3)
+        ref.step(3)
+        g = capture(b, n)
+        for eager in (0, 1, 2, 0):
+            g.replay()
+            b.step(eager)
+            ref.step(n + eager)
+            np.testing.assert_array_equal(b.poll()[0][slots[0]], ref.poll()[0][slots[1]])
+            for x, y in zip(*slots):
+                np.testing.assert_array_equal(b.state(x), ref.state(y))
+        b.close()
+        ref.close()
