@@ -170,11 +170,6 @@ void heap_give(adg_batch *b, size_t off, size_t bytes) {
   }
 }
 
-// Chains of launches that the detailed-chemistry instances are split over.
-int detailed_chains(const adg_batch *b, long long tiles) {
-  return tiles < kChainTiles ? 1 : std::min(b->group_streams, kChains);
-}
-
 // Work list: detailed instances first (by order, in as many groups as chains, of about equal tile
 // counts), then one-step instances by (order, flux, limiter).  Entries of one instance are consecutive.
 void rebuild_tiles(adg_batch *b) {
@@ -208,7 +203,7 @@ void rebuild_tiles(adg_batch *b) {
   std::stable_sort(det.begin(), det.end(), [&](int x, int y) { return order(x) > order(y); });
   long long total = 0, done = 0;
   for (int i : det) total += tiles_of(i);
-  const int chains = detailed_chains(b, total);
+  const int chains = total < kChainTiles ? 1 : kChains;
   size_t at = 0;
   for (int c = 0; c < chains && at < det.size(); ++c) {
     std::vector<int> part;
@@ -245,10 +240,17 @@ adg_status enqueue_batch_steps(adg_batch *b, hipStream_t st, int steps, bool tim
     BHIP(b, hipEventRecord(b->fork, st));
     for (int k = 1; k < nstreams; ++k) BHIP(b, hipStreamWaitEvent(b->aux[k - 1], b->fork, 0));
   }
+  // on one stream the chains of detailed-chemistry instances (the first groups) are one launch
+  int chains = 0, chained = 0;
+  if (nstreams <= 1)
+    for (const Group &g : b->groups)
+      if (g.kind == 0) { chains += 1; chained += g.n; }
   for (int step = 0; step < steps; ++step) {
     for (int stage = 0; stage < 3; ++stage) {
       for (int gi = 0; gi < (int)b->groups.size(); ++gi) {
-        const Group &g = b->groups[gi];
+        Group g = b->groups[gi];
+        if (gi < chains && gi > 0) continue;
+        if (gi < chains) g.n = chained;   // (the first group holds the largest order)
         if (g.kind == 1 && stage > 0) continue;   // its whole step ran in the first launch
         const hipStream_t gs = nstreams > 1 && gi % nstreams ? b->aux[gi % nstreams - 1] : st;
         hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -679,7 +681,6 @@ adg_status adg_batch_set_group_streams(adg_batch *b, int32_t streams) {
   if (streams < 1 || streams > kGroupStreams) return bfail(b, ADG_ERR_ARG, "group streams out of range");
   if (streams != b->group_streams) {
     b->group_streams = streams;
-    b->dirty = true;   // the groups depend on it
     destroy_batch_graph(b);   // captured with the old spread
   }
   return ADG_OK;

@@ -108,6 +108,7 @@ def test_batch_steps_in_a_graph(adg, n):
         slots = [[x.add(c, w, t) for (c, w), t in zip(cases, targets)] for x in (b, ref)]
         b.step(3)
         ref.step(3)
+        b.set_group_streams(2)   # after a step, and before the capture: nothing is left to prepare
         g = capture(b, n)
         for eager in (0, 1, 2, 0):
             g.replay()

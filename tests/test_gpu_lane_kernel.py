@@ -169,3 +169,23 @@ def test_reverse_rate_of_a_forward_rate_of_zero(adg, mech):
     print("[lane] Y / Y(0):", y.min(), y.max(), flush=True)
     assert y.max() < 0.99
     check(got, ref, case, 1e-10, "reverse rate")
+
+
+def test_chains_on_one_stream_and_on_two(adg, mech):
+    """Enough tiles (538) for two chains of launches, of different orders: one launch for both on one stream
+    and a stream each, bit for bit; the number of streams changed between steps."""
+    cases = [gen.case_c1(E=E, order_p=p, n_pe=9, mech=mech, cfl=CFL[p], Lx=0.01 * E / 2048) for E, p in ((8000, 4), (10000, 1))]
+    heap = sum(adg.Batch.instance_bytes(c) for c, _ in cases)
+    got = []
+    for streams in ((1, 1), (4, 4), (1, 2)):
+        b = adg.Batch(2, 18000, heap)
+        slots = [b.add(c, w) for c, w in cases]
+        for n in streams:
+            b.set_group_streams(n)
+            b.step(2)
+        assert b.profile(1)["detailed_stage"][1] == 3   # timed on one stream: a launch per stage
+        got.append([b.state(sl) for sl in slots])
+        b.close()
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            np.testing.assert_array_equal(x, y)
