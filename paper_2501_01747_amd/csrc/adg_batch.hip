@@ -227,19 +227,8 @@ adg_status ensure_group_streams(adg_batch *b) {
   return ADG_OK;
 }
 
-// `steps` time steps on stream st (timed: an event pair around every launch, all on one stream).
-// The groups hold disjoint instances and nothing passes between them, so with several groups each
-// runs its whole chain of launches side by side with the others (group k on stream k mod S, the
-// first on st), forked from st at the start and joined back into it at the end.
-adg_status enqueue_batch_steps(adg_batch *b, hipStream_t st, int steps, bool timed) {
-  if (steps <= 0) return ADG_OK;
-  const int nstreams = timed ? 1 : std::min<int>(b->group_streams, (int)b->groups.size());
-  if (nstreams > 1) {
-    adg_status rc = ensure_group_streams(b);
-    if (rc != ADG_OK) return rc;
-    BHIP(b, hipEventRecord(b->fork, st));
-    for (int k = 1; k < nstreams; ++k) BHIP(b, hipStreamWaitEvent(b->aux[k - 1], b->fork, 0));
-  }
+// The launches of enqueue_batch_steps, over `nstreams` streams that have been forked from st.
+adg_status launch_batch_steps(adg_batch *b, hipStream_t st, int nstreams, int steps, bool timed) {
   // on one stream the chains of detailed-chemistry instances (the first groups) are one launch
   int chains = 0, chained = 0;
   if (nstreams <= 1)
@@ -274,13 +263,32 @@ adg_status enqueue_batch_steps(adg_batch *b, hipStream_t st, int steps, bool tim
     }
     b->par ^= 1;   // the step's last launches wrote the next counts into the other counters
   }
-  if (nstreams > 1) {
-    for (int k = 1; k < nstreams; ++k) {
-      BHIP(b, hipEventRecord(b->join[k - 1], b->aux[k - 1]));
-      BHIP(b, hipStreamWaitEvent(st, b->join[k - 1], 0));
-    }
-  }
   return ADG_OK;
+}
+
+// `steps` time steps on stream st (timed: an event pair around every launch, all on one stream).
+// The groups hold disjoint instances and nothing passes between them, so with several groups each
+// runs its whole chain of launches side by side with the others (group k on stream k mod S, the
+// first on st), forked from st at the start and joined back into it at the end, also after a failed
+// launch: whoever waits for the batch's stream (a removal, an admission) waits for all of them.
+adg_status enqueue_batch_steps(adg_batch *b, hipStream_t st, int steps, bool timed) {
+  if (steps <= 0) return ADG_OK;
+  const int nstreams = timed ? 1 : std::min<int>(b->group_streams, (int)b->groups.size());
+  if (nstreams > 1) {
+    adg_status rc = ensure_group_streams(b);
+    if (rc != ADG_OK) return rc;
+    BHIP(b, hipEventRecord(b->fork, st));
+    for (int k = 1; k < nstreams; ++k) BHIP(b, hipStreamWaitEvent(b->aux[k - 1], b->fork, 0));
+  }
+  adg_status rc = launch_batch_steps(b, st, nstreams, steps, timed);
+  for (int k = 1; k < nstreams; ++k) {
+    hipError_t e = hipEventRecord(b->join[k - 1], b->aux[k - 1]);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, b->join[k - 1], 0);
+    if (e == hipSuccess) continue;
+    (void)hipStreamSynchronize(b->aux[k - 1]);
+    if (rc == ADG_OK) rc = bfail(b, ADG_ERR_HIP, std::string("joining the group streams: ") + hipGetErrorString(e));
+  }
+  return rc;
 }
 
 void destroy_batch_graph(adg_batch *b) {
