@@ -182,10 +182,10 @@ void destroy_graph(adg_solver *s) {
 adg_status capture_graph(adg_solver *s, int k, int cur0, int par0) {
   const int cur_keep = s->cur, par_keep = s->par;
   const bool at_keep = s->at_ready;
+  HIP_TRY(s, hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
   s->cur = cur0;
   s->par = par0;
   s->at_ready = false;   // whatever ran before a replay: its first launch reads no carried values
-  HIP_TRY(s, hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
   adg_status rc = ADG_OK;
   for (int i = 0; i < s->graph_steps && rc == ADG_OK; ++i) rc = enqueue_step(s, s->cap_stream, nullptr);
   s->graph_cur[k] = cur0;

@@ -345,13 +345,16 @@ adg_status build_batch_graph(adg_batch *b) {
   if (!b->cap_stream) BHIP(b, hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
   const int par_keep = b->par;
   for (int p = 0; p < 2; ++p) {
+    hipError_t e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) {
+      destroy_batch_graph(b);
+      return bfail(b, ADG_ERR_HIP, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
+    }
     b->par = p;
-    BHIP(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
-    adg_status rc = ADG_OK;
-    rc = enqueue_batch_steps(b, b->cap_stream, b->graph_steps, false);
+    adg_status rc = enqueue_batch_steps(b, b->cap_stream, b->graph_steps, false);
     b->par = par_keep;   // nothing ran: capture only records
     hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(b->cap_stream, &g);
+    e = hipStreamEndCapture(b->cap_stream, &g);
     if (rc != ADG_OK) {
       if (g) (void)hipGraphDestroy(g);
       destroy_batch_graph(b);

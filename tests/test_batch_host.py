@@ -79,3 +79,16 @@ def test_a_failed_launch_leaves_no_stream_behind(lib, at):
     assert "onestep" in calls and not unjoined(calls, "7"), calls
     lib.fake_fail(b"", -1)
     b.close()
+
+
+@pytest.mark.parametrize("name,at", [("begin", 0), ("begin", 1), ("onestep", 4), ("end", 1), ("instantiate", 1)])
+def test_a_failed_capture_keeps_the_parity(lib, name, at):
+    b = FakeBatch(lib, graph_steps=3)
+    lib.fake_fail(b"", -1)
+    assert b.parity() == 0
+    lib.fake_fail(name.encode(), at)
+    assert b.step(3) != 0
+    lib.fake_fail(b"", -1)
+    assert b.parity() == 0
+    assert b.step(3) == 0 and b.parity() == 1
+    b.close()
