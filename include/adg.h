@@ -228,7 +228,7 @@ int64_t adg_graph_replays(const adg_solver *s);
    (256, 512 or 1024 threads) of the stage kernel: every candidate is warmed up,
    then timed over n_reps launches of the first RK stage on the current state in
    three interleaved rounds, its fastest round counting; later steps use the
-   fastest candidate, or the first one (8/512) unless the fastest beats it by
+   fastest candidate, or the one chosen by size unless the fastest beats it by
    more than 3 %.  The timed launches only rewrite the first stage buffer and the
    current level's first-stage history, which the next step recomputes, so the
    solution is unchanged.  *choice (optional) receives the chosen candidate

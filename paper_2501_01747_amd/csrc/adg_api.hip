@@ -487,12 +487,13 @@ adg_status adg_autotune(adg_solver *s, int32_t n_reps, int32_t *choice) {
       HIP_TRY(s, hipEventElapsedTime(&ms, e0, e1));
       t[c] = std::min(t[c], (double)ms);
     }
-  int best = 0;
-  for (int c = 1; c < kNsConfigs; ++c)
+  // the decomposition that an untuned solver takes stays unless the fastest beats it by more than 3 %:
+  // candidates closer than that trade places from run to run (and under a profiler's dispatch overhead)
+  const int untuned = ns_kernel(s, -1) == kNsLane ? 1 : ns_kernel(s, -1);
+  int best = untuned;
+  for (int c = 0; c < kNsConfigs; ++c)
     if (t[c] < t[best]) best = c;
-  // the first decomposition stays unless the fastest beats it by more than 3 %: candidates
-  // closer than that trade places from run to run (and under a profiler's dispatch overhead)
-  if (t[best] > 0.97 * t[0]) best = 0;
+  if (t[best] > 0.97 * t[untuned]) best = untuned;
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   HIP_TRY(s, align(s, false));
