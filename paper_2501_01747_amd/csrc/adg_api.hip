@@ -467,6 +467,15 @@ adg_status adg_autotune(adg_solver *s, int32_t n_reps, int32_t *choice) {
   a.advance = 0;
   a.par = s->par;
   set_at_buffers(s, a, 0);   // writes only the successor's buffer, which the next step rewrites
+  if (s->P.at && !a.at_in) {
+    // The steps to come read carried AT values, so that is what is timed, also where no launch has left
+    // any: one that gathers leaves those of the next stage, of the same faces and delays.  The step after
+    // the tuning gathers.
+    HIP_TRY(s, launch_ns_stage(M, 0, a, mixed, s->stream));
+    double *other = s->P.at + (a.at_out == s->P.at ? s->P.at_stride : 0);
+    a.at_in = a.at_out;
+    a.at_out = other;
+  }
   // every candidate warmed up first, then timed in three interleaved rounds; each keeps
   // its fastest round (clock ramp-up and other transients then bias no candidate)
   double t[kNsConfigs];

@@ -53,3 +53,12 @@ def tune(lib, untuned, ms, steps=0):
 ])
 def test_the_untuned_kernel_stays_unless_another_is_faster(lib, untuned, ms, choice):
     assert tune(lib, untuned, ms)[0] == choice
+
+
+@pytest.mark.parametrize("steps", [0, 1])
+def test_candidates_are_timed_as_steps_run_them(lib, steps):
+    """With carried AT values, also before the first step: all but one launch that forms them."""
+    _, calls = tune(lib, 0, [9.0] * 6, steps)
+    timed = [c for c in calls if c.startswith(("carried", "gathered"))]
+    assert len(timed) == 5 * (2 + 3 * 4) + (1 - steps)
+    assert [c for c in timed if c.startswith("gathered")] == ([] if steps else ["gathered:0"])
