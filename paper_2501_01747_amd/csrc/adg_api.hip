@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <algorithm>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -52,7 +53,6 @@ struct adg_solver {
   std::vector<hipEvent_t> prof_events;
   std::string msg;
   int *host_err = nullptr;   // pinned: the error flag as adg_get_state's kernel stores it (null: copied instead)
-  int reads = 0;             // states read so far, up to 2
   int noalloc_dev = -1;   // device whose static scratch holds this solver (adg_create_noalloc), else -1
 };
 
@@ -70,6 +70,44 @@ constexpr int kMaxDevices = 64;
 void *g_scratch_ptr[kMaxDevices] = {};   // device address of `scratch` per device (hipGetSymbolAddress)
 adg_solver g_noalloc_solver[kMaxDevices];
 bool g_noalloc_busy[kMaxDevices] = {};
+
+// Pinned words that adg_get_state's kernels store the error flag in beside the state, so that one wait gives
+// both (16 us for a small state on the device, 25 with the flag copied after it).  One block for the process,
+// since allocating pinned memory takes as long as many reads (40 to 400 us), handed out word by word: taken at
+// a solver's first read, given back by adg_destroy.  A process that reads one state never allocates it, and
+// solvers beyond its words copy their flags.
+class FlagWords {
+ public:
+  int *take() {
+    std::lock_guard<std::mutex> lock(m_);
+    if (reads_ < 1) { reads_ += 1; return nullptr; }
+    if (!block_) {
+      if (hipHostMalloc((void **)&block_, kWords * kStride * sizeof(int), hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        block_ = nullptr;
+        return nullptr;
+      }
+      for (int i = kWords - 1; i >= 0; --i) free_.push_back(block_ + i * kStride);
+    }
+    if (free_.empty()) return nullptr;
+    int *p = free_.back();
+    free_.pop_back();
+    return p;
+  }
+  void give(int *p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> lock(m_);
+    free_.push_back(p);
+  }
+
+ private:
+  static constexpr int kWords = 64, kStride = 16;   // a cache line each
+  std::mutex m_;
+  int *block_ = nullptr;
+  int reads_ = 0;
+  std::vector<int *> free_;
+};
+FlagWords &g_flags = *new FlagWords;   // never destroyed: solvers may outlive static objects
 
 adg_status fail(adg_solver *s, adg_status code, const std::string &m) {
   if (s) s->msg = m;
@@ -362,15 +400,7 @@ adg_status adg_get_state(adg_solver *s, double *w, int64_t count, int32_t where)
   if (!s || !w) return ADG_ERR_ARG;
   const Layout &L = s->P.lay;
   if (count != (int64_t)L.E * L.V * L.M) return fail(s, ADG_ERR_ARG, "state size mismatch");
-  // From the second read on, the kernel that changes the layout stores the error flag in pinned host
-  // memory, so one wait gives both: 6 to 10 us less for each read, but 25 us and more (250 in a process
-  // that has just freed memory) to allocate, which a state that is read once would not earn back.
-  if (!s->host_err && s->noalloc_dev < 0 && s->reads == 1 &&
-      hipHostMalloc((void **)&s->host_err, sizeof(int), hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    s->host_err = nullptr;
-  }
-  s->reads = std::min(s->reads + 1, 2);
+  if (!s->host_err && s->noalloc_dev < 0) s->host_err = g_flags.take();
   HIP_TRY(s, align(s, true));
   if (where == ADG_HOST) {
     HIP_TRY(s, get_state_host(s->P, s->P.W[s->cur], w, s->host_err, s->stream));
@@ -539,7 +569,7 @@ void adg_destroy(adg_solver *s) {
   destroy_graph(s);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   s->cap_stream = nullptr;
-  if (s->host_err) (void)hipHostFree(s->host_err);
+  g_flags.give(s->host_err);
   s->host_err = nullptr;
   if (s->noalloc_dev >= 0) {
     g_noalloc_busy[s->noalloc_dev] = false;   // the static solver and scratch are free again

@@ -52,7 +52,7 @@ hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, hipGraphNode_t *, 
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t s) { return call("graph", s); }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = malloc(n); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = malloc(n); return call("pinned", nullptr); }
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "failed"; }
@@ -89,7 +89,10 @@ bool capturing(hipStream_t) { return false; }
 hipError_t launch_level_counts(long long *, int, hipStream_t) { return hipSuccess; }
 hipError_t set_state_device(const Problem &, const double *, hipStream_t, const Copies *) { return hipSuccess; }
 hipError_t set_state_host(const Problem &, const double *, hipStream_t, const Copies *) { return hipSuccess; }
-hipError_t get_state_device(const Problem &, const double *, double *, int *, hipStream_t, const long long *) { return hipSuccess; }
+hipError_t get_state_device(const Problem &, const double *, double *, int *flag, hipStream_t, const long long *) {
+  if (flag) *flag = 0;
+  return call("read", flag);
+}
 hipError_t get_state_host(const Problem &, const double *, double *, int *, hipStream_t, const long long *) { return hipSuccess; }
 template <int NSC>
 adg_status ns_build_mech(const adg_physics *, NsMechT<NSC> &) { return ADG_OK; }

@@ -62,3 +62,33 @@ def test_candidates_are_timed_as_steps_run_them(lib, steps):
     timed = [c for c in calls if c.startswith(("carried", "gathered"))]
     assert len(timed) == 5 * (2 + 3 * 4) + (1 - steps)
     assert [c for c in timed if c.startswith("gathered")] == ([] if steps else ["gathered:0"])
+
+
+def test_pinned_words_of_the_error_flags(lib):
+    """One pinned block for all solvers of the process: none for the first read, then a word each from a
+    solver's next read on, handed on after adg_destroy, and the flag copied where none is left."""
+    case, w0 = gen.case_c1(E=16, n_pe=2, Lx=0.01 * 16 / 2048)
+    p, mem = adg.Problem(case), C.create_string_buffer(4096)
+    base = (C.addressof(mem) + 255) & ~255
+    w = (C.c_double * w0.size)()
+
+    def solver():
+        h = C.c_void_p()
+        assert lib.adg_create(C.byref(p.phys), C.byref(p.disc), C.byref(p.asyn), C.c_void_p(base), C.c_size_t(2048),
+                              C.c_void_p(7), C.byref(h)) == 0
+        return h
+
+    def read(h):
+        assert lib.adg_get_state(h, w, C.c_int64(w0.size), 1) == 0
+        return [c for c in lib.fake_calls().decode().split() if c.startswith("read")][-1]
+
+    lib.fake_fail(b"", -1)
+    many = [solver() for _ in range(70)]
+    words = [read(h) for h in many]
+    assert words[0] == "read:0" and len(set(words[1:65])) == 64 and set(words[65:]) == {"read:0"}
+    assert [read(h) for h in many[1:65]] == words[1:65]
+    lib.adg_destroy(many[5])
+    assert read(many[0]) == words[5] and read(many[69]) == "read:0"
+    assert lib.fake_calls().decode().split().count("pinned:0") == 1
+    for h in many[:5] + many[6:]:
+        lib.adg_destroy(h)
