@@ -135,6 +135,7 @@ __device__ __forceinline__ void ns_lane_tile(const NsArgs &a, const double *__re
   constexpr int V = G::V, Q = M, NF = G::NF, NN = G::NN, T0 = G::T0, NP = G::NP, NTH = G::NTH, NI = G::NI;
   // constant address space: uniform reads become scalar loads whatever is stored in between
   const auto *mk = (const __attribute__((address_space(4))) NsMechT<NS> *)(uintptr_t)a.mech;
+  constexpr int kLines = (int)((sizeof mk->sp + 24 * sizeof mk->rx[0]) / 64), kPre = (kLines + G::NW - 1) / G::NW;
   const int t = threadIdx.x;
   const int E = a.E, Vg = 3 + a.ns, VMg = Vg * M;
   const int nloc = min(TE, E - e0);
@@ -178,6 +179,19 @@ __device__ __forceinline__ void ns_lane_tile(const NsArgs &a, const double *__re
     else if (x >= E) { x = E - 1; el = E - 1 - e0; r = Q; }
   }
 
+  // The mechanism's records into the scalar cache: a wavefront of a small launch would miss on each in turn
+  // (16 species, E = 2^16, N_p = 3: 100 -> 86 us a stage).  The loads go out before those of the modes, in
+  // whose shadow they return; issued after them, the wait took 3800 of a tile's 41000 cycles (batches of
+  // up to 150 tiles 55 -> 51.5 us a step, E = 2^18 153 -> 149 a stage, and 1024 instances 602 -> 565).
+  int pre[kPre];
+  {
+    const auto *line = (const __attribute__((address_space(4))) int *)(uintptr_t)&static_cast<const NsMechT<NS> *>(a.mech)->sp[0];
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+#pragma unroll
+    for (int i = 0; i < kPre; ++i) pre[i] = line[min(w + i * G::NW, kLines - 1) * 16];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
   // values at the point and the volume part of the gradient there, from the element's modes
   double X[V], D[V];
   {
@@ -215,17 +229,9 @@ __device__ __forceinline__ void ns_lane_tile(const NsArgs &a, const double *__re
     }
     pin(X);
     pin(D);
-  }
-  // the mechanism's records into the scalar cache while the modes are on their way (a wavefront of a
-  // small launch would miss on each in turn: 16 species, E = 2^16, N_p = 3: 100 -> 86 us)
-  {
-    const auto *line = (const __attribute__((address_space(4))) int *)(uintptr_t)&static_cast<const NsMechT<NS> *>(a.mech)->sp[0];
-    constexpr int kLines = (int)((sizeof mk->sp + 24 * sizeof mk->rx[0]) / 64);
-    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    int acc = 0;
 #pragma unroll
-    for (int i = 0; i < (kLines + G::NW - 1) / G::NW; ++i) acc ^= line[min(w + i * G::NW, kLines - 1) * 16];
-    asm volatile("" ::"s"(acc));
+    for (int i = 1; i < kPre; ++i) pre[0] ^= pre[i];
+    asm volatile("" ::"s"(pre[0]));
   }
   if (t >= T0 && t < G::NL) {
 #pragma unroll
