@@ -189,3 +189,43 @@ def test_chains_on_one_stream_and_on_two(adg, mech):
     for other in got[1:]:
         for x, y in zip(got[0], other):
             np.testing.assert_array_equal(x, y)
+
+
+def test_inviscid(adg, orc, mech):
+    run_batch(adg, orc, [gen.case_c1(E=E, order_p=p, n_pe=4, mech=mech, cfl=CFL[p], Lx=0.01 * E / 2048, viscous=0)
+                         for E, p in ((70, 3), (47, 1))], 10)
+
+
+def test_graphs_across_a_change_of_decomposition(adg, mech):
+    """A large single problem stepped from graphs, by the lane-per-point kernel, by a spread one, which carries AT
+    values from launch to launch, and by the former again: bit for bit the plain steps."""
+    case, w0 = gen.case_c1(E=8215, n_pe=120, mech=mech, Lx=0.01 * 8215 / 2048, cfl=0.02)
+    got = []
+    for graph in (0, 2, 3):
+        s = adg.Solver(case)
+        s.set_graph(graph)
+        s.set_state(w0)
+        for config, n in ((None, 5), (0, 4), (1, 5), (0, 3)):
+            if config is not None:
+                s.set_kernel_config(config)
+            s.step(n)
+        assert s.step_count() == 17 and (s.graph_replays > 0) == (graph > 0)
+        got.append(s.state())
+        s.close()
+    for w in got[1:]:
+        np.testing.assert_array_equal(w, got[0])
+
+
+def test_factors_beyond_the_factored_range_of_a_large_mechanism(adg, orc):
+    """As above with 16 species: a single problem of a size that takes this kernel."""
+    mech = mechanism_of(16)
+    nasa = mech["nasa7"].copy()
+    nasa[:, 5] -= 0.6e6 / gen.RU * mech["composition"][:, 0]
+    case, w0 = gen.case_c1(E=12300, order_p=1, n_pe=5, mech=dict(mech, nasa7=nasa), Lx=0.01 * 12300 / 2048, cfl=0.05)
+    s = adg.Solver(case)
+    s.set_state(w0)
+    s.step(3)
+    o = orc.OracleSolver(case, w0, 4)
+    o.step(3)
+    check(s.state(), o.state(), case, 1e-10, "16 species")
+    s.close()
