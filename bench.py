@@ -91,17 +91,6 @@ def launches_per_step(case) -> int:
 
 
 def euler_stage_bytes(case) -> float:
-    """Algorithmic HBM bytes of one launch per stage, averaged over the three stages:
-    stage 1 reads w^n and writes w^(1) (16 B/DOF); stages 2 and 3 read w^n and
-    w^(s) and write w^(s+1) (24 B/DOF); with the limiter (inside the same kernel)
-    one troubled-cell flag byte per element."""
-    from workloads import gen
-
-    flags = case["disc"]["n_elem"] if case["disc"].get("limiter") else 0
-    return gen.dof(case) * 8.0 * (2 + 3 + 3) / 3.0 + flags
-
-
-def euler_stage_bytes(case) -> float:
     """Algorithmic HBM bytes of a stage where each is a launch of its own, averaged over the three
     stages: stage 1 reads w^n and writes w^(1) (16 B/DOF); stages 2 and 3 read w^n and w^(s) and
     write w^(s+1) (24 B/DOF); with the limiter one troubled-cell flag byte per element."""
@@ -146,6 +135,25 @@ def detailed_stage_flops(case) -> float:
     elem = 2 * M * (Q + 2) * V + 4 * M * M * V + 2 * M * Q * (V + ns) + 8 * M * V
     face = 6 * V + 8 + 2 * V
     return float(E * ((Q + 2) * point + Q * chem + elem + face))
+
+
+# what shapes each kernel: a traffic summary holds while all of it is as it was
+COMMON_SRC = ["adg_device.hpp", "adg_internal.hpp"]
+EULER_SRC = ["adg_euler.hip", *COMMON_SRC]
+NS_SRC = ["adg_ns.hip", "adg_ns.hpp", "adg_ns_device.hpp", *COMMON_SRC]
+NS_LANE_SRC = ["adg_ns_lane.hip", "adg_ns.hpp", "adg_ns_device.hpp", *COMMON_SRC]
+
+
+def detailed_kernel(case, config: int):
+    """The kernel that decomposition `config` of a detailed-chemistry problem runs, and its sources."""
+    large = case["disc"]["n_elem"] > (8192 if case["physics"]["n_species"] <= 9 else 12288)
+    return ("ns_lane_kernel", NS_LANE_SRC) if config == 1 and large else ("ns_stage_kernel", NS_SRC)
+
+
+def onestep_bound(case) -> str:
+    """What bounds a launch of the one-step model: up to one wavefront on each of 1024 SIMDs (of 58 owned
+    elements, 52 with the limiter) the latency of one, beyond that instruction issue."""
+    return "latency" if case["disc"]["n_elem"] <= 1024 * (52 if case["disc"].get("limiter") else 58) else "alu"
 
 
 def src_hash(files) -> str:
@@ -314,7 +322,7 @@ def bench_batched(steps: int, warmup: int, graph: int, precision: str = "mixed",
         "state_errors": int(er.sum()), "steps_done_min": int(st[st >= 0].min()),
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_VECTOR_PEAK_TFLOPS,
-                     "traffic": read_traffic("c3", ["adg_ns_lane.hip", "adg_ns.hpp"]), "kernel": "ns_lane_batch_kernel",
+                     "traffic": read_traffic("c3", NS_LANE_SRC), "kernel": "ns_lane_batch_kernel",
                      "launch_ms": stage_ms, "flops_per_launch": flops},
     }
     if cpu:
@@ -395,9 +403,9 @@ def hbm_points(steps: int = 20):
                                    ("c2_physics_E2097152", sweep_limiter([2**21], steps)[0], "euler_lim_step_kernel",
                                     "c2_2097152")):
         out[key] = {"n_elem": res["n_elem"], "dof": res["dof"], "launch_ms": res["stage_ms"],
-                    "roofline": {"bound": "hbm", "kernel": kernel, "achieved": res["GBps"], "peak": HBM_PEAK_GBS,
+                    "roofline": {"bound": "alu", "roof": "hbm", "kernel": kernel, "achieved": res["GBps"], "peak": HBM_PEAK_GBS,
                                  "unit": "GB/s", "frac": res["frac_hbm"], "bytes_per_launch": res["bytes"],
-                                 "traffic": read_traffic(tkey, ["adg_euler.hip", "adg_device.hpp"])}}
+                                 "traffic": read_traffic(tkey, EULER_SRC)}}
     return out
 
 
@@ -626,18 +634,18 @@ def main():
     # each launch alone between its own pair of events (includes its dispatch), for reference
     prof = s.profile(max(10, min(args.steps, 50)))
     detailed = case["physics"]["model"] == "detailed"
-    kernel_src = ["adg_ns.hip", "adg_ns.hpp"] if detailed else ["adg_euler.hip", "adg_device.hpp"]
+    kernel, kernel_src = detailed_kernel(case, tuned) if detailed else ("", EULER_SRC)
     traffic_key = args.workload if args.n_elem is None else f"{args.workload}_{args.n_elem}"
     if detailed:
         flops = detailed_stage_flops(case)
         achieved = flops / (stage_ms * 1e-3) / 1e12
         roof = {"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / FP64_VECTOR_PEAK_TFLOPS, "traffic": read_traffic(traffic_key, kernel_src),
-                "kernel": "ns_stage_kernel", "launch_ms": stage_ms, "flops_per_launch": flops}
+                "kernel": kernel, "launch_ms": stage_ms, "flops_per_launch": flops}
     else:
         nbytes = euler_launch_bytes(case)
         achieved = nbytes / (stage_ms * 1e-3) / 1e9
-        roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        roof = {"bound": onestep_bound(case), "roof": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": read_traffic(traffic_key, kernel_src),
                 "kernel": "euler_lim_step_kernel" if case["disc"].get("limiter") else "euler_step_kernel",
                 "launch_ms": stage_ms, "bytes_per_launch": nbytes}

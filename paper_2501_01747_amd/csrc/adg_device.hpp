@@ -109,12 +109,14 @@ __device__ __forceinline__ void advance_step(long long *step, int par, long long
 }
 
 // ---------------------------------------------------------------- elementary functions
+// The errors stated are the largest of 4 million arguments drawn from each range, against 64-bit-mantissa
+// arithmetic.
 // ln 2 to 42 bits (its product with an exponent is exact) and the rest.
 constexpr double kLn2Hi = 0x1.62e42fefa3800p-1, kLn2Lo = 0x1.ef35793c76730p-45, kInvLn2 = 1.4426950408889634;
 
 // exp(x): k = rint(x / ln 2), r = x - k ln 2 in two parts, the Taylor polynomial of degree 13 in
 // |r| <= ln(2)/2 (its remainder is below 2^-57 of the result), 2^k by ldexp, which saturates to 0
-// and infinity.  For finite arguments.
+// and infinity.  For arguments of a size below 2^30; 0.89 ulp on |x| <= 700.
 __device__ __forceinline__ double exp_taylor(double x) {
   const double k = __builtin_rint(x * kInvLn2);
   double r = fma(k, -kLn2Hi, x);
@@ -137,7 +139,7 @@ __device__ __forceinline__ double exp_taylor(double x) {
 }
 
 // exp_taylor with its polynomial split by powers of r^2, r^4 and r^8: two more multiplications, and half
-// of the dependent chain, for where one wavefront waits for one value.
+// of the dependent chain, for where one wavefront waits for one value.  1.73 ulp on |x| <= 700.
 __device__ __forceinline__ double exp_short(double x) {
   const double k = __builtin_rint(x * kInvLn2);
   double r = fma(k, -kLn2Hi, x);
@@ -150,7 +152,8 @@ __device__ __forceinline__ double exp_short(double x) {
   return __builtin_amdgcn_ldexp(fma(r4, fma(r8, d, fma(r4, c, b)), a), (int)k);
 }
 
-// 1/x by the hardware estimate and two Newton steps, for x away from the ends of the range.
+// 1/x by the hardware estimate and two Newton steps, for x away from the ends of the range: correctly
+// rounded but for rare last bits (0.500 ulp on 1e-300 .. 1e300).
 __device__ __forceinline__ double recip(double x) {
   double y = __builtin_amdgcn_rcp(x);
   y = fma(fma(-x, y, 1.0), y, y);
@@ -159,7 +162,8 @@ __device__ __forceinline__ double recip(double x) {
 
 // log(x) of a normal positive x: x = 2^k m with sqrt(1/2) <= m < sqrt(2), s = (m-1)/(m+1), and
 // log m = 2 artanh s by its series up to s^19 (|s| < 0.172: the rest is below 2^-55 of log m),
-// split like exp_short's polynomial.  An infinite or NaN x gives NaN.
+// split like exp_short's polynomial.  An infinite or NaN x gives NaN.  0.63 ulp on 200 .. 6000 (the
+// temperatures it is used for), up to 2.5 ulp around 1, where log x is small.
 __device__ __forceinline__ double log_short(double x) {
   double m = __builtin_amdgcn_frexp_mant(x);
   int k = __builtin_amdgcn_frexp_exp(x);
@@ -173,8 +177,9 @@ __device__ __forceinline__ double log_short(double x) {
   return fma((double)k, kLn2Hi, s2 + fma(s2 * z, p, (double)k * kLn2Lo));
 }
 
-// Square root of a positive x from the hardware's estimate of 1/sqrt(x): two coupled Newton steps for
-// the root g and half its reciprocal h, then the remainder x - g^2 folded in.
+// Square root of a positive x from the hardware's estimate of 1/sqrt(x): one coupled step for the root g
+// and half its reciprocal h (Goldschmidt's iteration), then the remainder x - g^2 folded in twice.  0.500
+// ulp on 1e-290 .. 1e290.
 __device__ __forceinline__ double root(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;

@@ -832,7 +832,7 @@ __device__ __forceinline__ void ns_tile(const NsArgs &a, const double *__restric
     const double L = 2.0 * a.inv_dx * (half2j1 * b) + half2j1 * src;
     const size_t gi = sidx(e0 + el, c, VMg);
     double o;
-    // explicit fused multiply-adds: the single-problem and batched kernels round alike
+    // explicit fused multiply-adds: every decomposition rounds alike here
     if (rk.two_n) {
       const double kn = use_prev ? fma(rk.ca, w0pre[m], a.dt * L) : a.dt * L;
       kbuf[gi] = kn;
@@ -1054,14 +1054,17 @@ static int tiles_per_cu(int M) {
 // Measured (us per stage, one box, N_p = 3, 9 species; 8/512, 8/256, a lane per point):
 //   E = 2048   9.8 11.1 18.2     E = 4096   12.3 12.9 18.5     E = 6144  18.8 14.9 18.6
 //   E = 8192  21.6 16.3 20.0     E = 12288  31.3 24.9 20.5     E = 2^15  77.2 53.1 30.5
-// and the same lines for N_p = 1, 2, 4.  While a CU has no more than one tile of 4, that tile is the
+// and the same lines for N_p = 1 and 2.  While a CU has no more than one tile of 4, that tile is the
 // shortest chain: 8/512 and 4/512 take 9.2 and 8.7 at E = 16, 9.3 and 8.9 at E = 1024 (N_p = 4: 9.9 and
 // 9.2 at 150; 16 species, N_p = 4: 11.8 and 10.0 at 1024), but 9.5 and 10.0 at E = 1400.
 // While all tiles of 8 are resident at once the spread kernels win: their latency per tile is about half
 // of a lane's that forms every species and reaction of its point; 512 threads while two tiles a CU
-// hold the problem (256 CUs), 256 threads while the LDS holds it.  Beyond, the lane-per-point kernel's fewer instructions do, with 16 species from 12288 elements
-// on (a lane's chain is longer: 16384 elements at N_p = 3 take 46.6, 53.0 and 34.4, 8192 take 25.2,
-// 27.8 and 29.7).
+// hold the problem (256 CUs), 256 threads while the LDS holds it.  Beyond, the lane-per-point kernel's
+// fewer instructions do, from 8192 elements on (with 16 species from 12288: a lane's chain is longer:
+// 16384 elements at N_p = 3 take 46.6, 53.0 and 34.4, 8192 take 25.2, 27.8 and 29.7).
+// In between, where the LDS holds fewer tiles than there are (N_p = 4 from 6145 elements, 16 species from
+// 4097 or 6145), 8/512 goes in two rounds and stays: N_p = 4, 9 species, E = 6200 21.0 22.1 22.5, 8192
+// 22.2 23.3 22.4; 16 species at N_p = 2, E = 6200 21.0 and 22.5, N_p = 4, 10000 34.1 and 41.5 (8/512, 8/256).
 int ns_kernel_of(int cfg, int E, int M, int ns) {
   constexpr int kCus = 256;
   const bool wide = ns_capacity(ns) > kNsMaxSpecies;

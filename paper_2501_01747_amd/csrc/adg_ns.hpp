@@ -13,7 +13,9 @@ constexpr int kNsMaxSpecies = 9;      // the batched kernel, and single problems
 constexpr int kNsWideSpecies = 16;    // single problems with 9 < Ns <= 16
 constexpr int kNsMaxReactions = 32;
 constexpr int kNsReactionGroup = 2;   // reactions that a lane of the lane-per-point kernels forms side by side
-constexpr int kNsBatchReactions = 24;   // reactions of a batched mechanism
+// Reactions of a batched mechanism.  The batched kernel could take kNsMaxReactions; the limit is the one that
+// adg.h states, which callers may rely on for the refusal.
+constexpr int kNsBatchReactions = 24;
 // Ea/Ru (K) from which a reaction has no rate in either direction at any temperature of the thermo
 // (exp underflows by 2000 and more at 5e5 K), and the size of ln k_f up to which the lane-per-point
 // kernels form a reverse rate from k_f.
@@ -148,6 +150,8 @@ int ns_lane_tile_elems(int M);
 hipError_t launch_ns_lane(int M, const NsArgs &a, hipStream_t s);
 hipError_t launch_ns_lane_batch(int max_m, const NsArgs *insts, const int2 *tiles, int ntiles, int stage, int par,
                                 hipStream_t s);
+// Elements per work item that a batch's header is sized for: smaller than any tile, so that a header's size,
+// which callers keep, does not depend on the kernels' tiles.
 constexpr int kNsMinTile = 4;
 
 }  // namespace adg
