@@ -181,7 +181,10 @@ adg_status adg_create(const adg_physics *phys, const adg_discretization *disc, c
    device error flag. */
 adg_status adg_set_state(adg_solver *s, const double *w, int64_t count, int32_t where);
 
-/* Enqueue n_steps full SSP-RK3 time steps on the stream (asynchronous). */
+/* Enqueue n_steps full time steps on the stream (asynchronous).  A caller that is
+   capturing the stream into a HIP graph of its own gets them into the graph;
+   replays, eager steps and new states may then follow in any order (a solver
+   that has been captured pays two small launches per call). */
 adg_status adg_step(adg_solver *s, int32_t n_steps);
 
 /* Copy the current state out ([E][V][M]).  Synchronises the stream and
@@ -321,7 +324,8 @@ adg_status adg_batch_add(adg_batch *b, const adg_physics *phys, const adg_discre
 adg_status adg_batch_remove(adg_batch *b, int32_t slot);
 
 /* Enqueue n_steps time steps of every admitted instance that has not reached
-   its n_steps (asynchronous). */
+   its n_steps (asynchronous; into a graph that the caller is capturing, as with
+   adg_step, provided that no instance was added or removed since the last step). */
 adg_status adg_batch_step(adg_batch *b, int32_t n_steps);
 
 /* Synchronise; steps[i] = completed time steps of slot i (-1 if empty) and

@@ -401,7 +401,7 @@ adg_status adg_get_state(adg_solver *s, double *w, int64_t count, int32_t where)
   const Layout &L = s->P.lay;
   if (count != (int64_t)L.E * L.V * L.M) return fail(s, ADG_ERR_ARG, "state size mismatch");
   if (!s->host_err && s->noalloc_dev < 0) s->host_err = g_flags.take();
-  HIP_TRY(s, align(s, true));
+  if (s->captured) HIP_TRY(s, align(s, true));   // (this call waits, so it is never captured itself)
   if (where == ADG_HOST) {
     HIP_TRY(s, get_state_host(s->P, s->P.W[s->cur], w, s->host_err, s->stream));
   } else if (where == ADG_DEVICE) {
