@@ -442,8 +442,8 @@ constexpr int owned_lanes() { return 64 - 2 * S * (LIM ? 2 : 1); }
 // all that a delayed face reads from the ring, and those precede the step, so they are gathered for
 // every stage at the start, beside the state loads, and kept in LDS.
 //   Without the limiter, N_p = 2, against one launch per stage: 9.6 us per step against 21.7 at
-// E = 512 (launch and latency bound), 0.26 ms against 0.78 at E = 2^22 (was bound by HBM at 5.2 TB/s;
-// now by the FP64 issue rate, 3.8 TB/s of the one read and one write).  Instructions decide both, so
+// E = 512 (launch and latency bound), 0.27 ms against 0.78 at E = 2^22 in a steady run (was bound by HBM at
+// 5.2 TB/s; now by the FP64 issue rate, 3.7 TB/s of the one read and one write).  Instructions decide both, so
 // the Legendre values that are 0 or 1 are left out, the factors of dt L are folded into one per mode,
 // and recip, root and exp_taylor stand for the general division, square root and exponential (0.33 ms
 // and 11.1 us without that).
@@ -732,6 +732,10 @@ template <bool LIM>
 constexpr int kEulerWaves = LIM ? 1 : 4;
 // Wavefronts per SIMD that the registers are held to.  Without a bound N_p = 4 takes 262 registers, one
 // wavefront: 216 us per step at E = 2^20, 158 with two (15.6 and 16.0 at E = 4000, where there is one).
+// With the limiter the 2N schemes hold a register beside the state and spill for it (104 bytes a lane at
+// N_p = 2, 160 at N_p = 4); per step against one launch per stage, HLLC and KXRCF: RK2 at E = 500 000
+// 62.8 us against 96.0 (N_p = 2) and 116 against 224 (N_p = 4), LSERK4 146 against 248 and 281 against 582;
+// at E = 8192 19.9 against 30.8 (RK2, N_p = 2) and 66.5 against 137 (LSERK4, N_p = 4).
 template <int M, bool LIM>
 constexpr int kEulerMinWaves = LIM ? (M <= 3 ? 3 : 2) : M == 5 ? 2 : 1;
 template <int M, int S, bool LIM>
