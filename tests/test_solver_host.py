@@ -6,7 +6,6 @@ import subprocess
 
 import pytest
 
-from paper_2501_01747_amd import adg
 from workloads import gen
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -27,6 +26,8 @@ def lib(tmp_path_factory):
 
 def tune(lib, untuned, ms, steps=0):
     """The choice and the calls of a tuning whose untuned kernel is `untuned`; ms: the times of the kernels 0..5."""
+    from paper_2501_01747_amd import adg   # (not with the module: a test run on a GPU loads torch's runtime first)
+
     case, _ = gen.case_c1(E=16, n_pe=2, Lx=0.01 * 16 / 2048)
     p, h, mem = adg.Problem(case), C.c_void_p(), C.create_string_buffer(4096)
     base = (C.addressof(mem) + 255) & ~255
@@ -67,6 +68,8 @@ def test_candidates_are_timed_as_steps_run_them(lib, steps):
 def test_pinned_words_of_the_error_flags(lib):
     """One pinned block for all solvers of the process: none for the first read, then a word each from a
     solver's next read on, handed on after adg_destroy, and the flag copied where none is left."""
+    from paper_2501_01747_amd import adg
+
     case, w0 = gen.case_c1(E=16, n_pe=2, Lx=0.01 * 16 / 2048)
     p, mem = adg.Problem(case), C.create_string_buffer(4096)
     base = (C.addressof(mem) + 255) & ~255
