@@ -93,10 +93,10 @@ struct LaneLds {
   };
 };
 
-// The tile's faces: interface index (or -1), effective delay, and the number of interfaces.
+// The tile's faces: interface index (or -1) and effective delay; and the n faces that are interfaces.
 template <int NF>
 struct LanePe {
-  int i[NF], k[NF], n;
+  int i[NF], k[NF], f[NF], n;
 };
 
 // AT combination (Eq. (7)) of the central trace and the flux of variable v at interface i from the
@@ -241,13 +241,13 @@ __device__ __forceinline__ void ns_lane_tile(const NsArgs &a, const double *__re
     }
   }
   int kf = 0;
-  unsigned long long pe_mask = 0;   // the first wavefront's: faces that are PE interfaces
   if (t < 64) {
     kf = fi >= 0 ? eff_delay<true>(a.dl, n, fi) : 0;
-    pe_mask = __ballot(fi >= 0);
+    const unsigned long long pe_mask = __ballot(fi >= 0);
     if (t < NF) {
       P.i[t] = fi;
       P.k[t] = kf;
+      if (fi >= 0) P.f[__popcll(pe_mask & ((1ull << t) - 1ull))] = t;
     }
     if (t == 0) P.n = __popcll(pe_mask);
   }
@@ -265,27 +265,23 @@ __device__ __forceinline__ void ns_lane_tile(const NsArgs &a, const double *__re
   const int iface = trace ? P.i[fl] : -1;
   const int npe = __builtin_amdgcn_readfirstlane(P.n);
   if (npe) {
-    // one lane of the first wavefront per (interface, variable): the synchronous central trace of an
-    // owned interface is published for this level; the AT combinations (Eq. (7)) of a delayed one's
-    // central trace and flux are formed together, the flux goes to its place and the central trace
-    // corrects the gradients of the two elements, but for the interface's own traces: their flux is
-    // the synchronous one, published
-    if (t < 64) {
-      for (int i0 = 0; i0 < npe * V; i0 += 64) {
-        const int slot = (i0 + t) / V, v = (i0 + t) % V;
-        unsigned long long m = pe_mask;
-        for (int j = 0; j < slot && m; ++j) m &= m - 1;
-        const int g = m ? __ffsll((long long)m) - 1 : 0;
-        const int i = __shfl(fi, g), k = __shfl(kf, g);
-        if (m && v < Vg) {
-          const double wc = 0.5 * (L.f.tl[v][g] + L.f.tr[v][g]);
-          if (g >= 1 && g <= nloc) ring_at(a.ring, nm, stage, a.dl.nif, i)[a.ring.off_Wc + v] = wc;
-          if (k > 0) {
-            double aw, af;
-            at_levels(a, q_at, k, nm, stage, i, v, aw, af);
-            if (g >= 1 && g <= TE + 1) L.F[v][g - 1] = af;
-            L.f.dw[v][g] = aw - wc;
-          }
+    // one lane per (interface, variable): the synchronous central trace of an owned interface is
+    // published for this level; the AT combinations (Eq. (7)) of a delayed one's central trace and flux
+    // are formed together, the flux goes to its place and the central trace corrects the gradients of the
+    // two elements, but for the interface's own traces: their flux is the synchronous one, published.
+    // Every wavefront takes pairs: with the first one alone, 9000 elements with a PE interface at every face
+    // took 108 us a step at N_p = 2 and 142 with q = 6 levels, against 69 and 83 (tiles spread over lanes: 81
+    // and 95); one face in 16, 63.7 and 60.2.
+    for (int p = t; p < npe * V; p += NTH) {
+      const int g = P.f[p / V], v = p % V, i = P.i[g], k = P.k[g];
+      if (v < Vg) {
+        const double wc = 0.5 * (L.f.tl[v][g] + L.f.tr[v][g]);
+        if (g >= 1 && g <= nloc) ring_at(a.ring, nm, stage, a.dl.nif, i)[a.ring.off_Wc + v] = wc;
+        if (k > 0) {
+          double aw, af;
+          at_levels(a, q_at, k, nm, stage, i, v, aw, af);
+          if (g >= 1 && g <= TE + 1) L.F[v][g - 1] = af;
+          L.f.dw[v][g] = aw - wc;
         }
       }
     }
