@@ -12,12 +12,12 @@
 // operands, with no table in LDS and no index arithmetic per lane, and the species production is
 // summed in registers.
 //
-// The stage is bound by the VALU issue rate (67 % of a stage of 4096 instances) and, at five tiles a CU, by
+// The stage is bound by the VALU issue rate (66 % of a stage of 4096 instances) and, at five tiles a CU, by
 // the latency of the phases between its barriers; with few tiles, by that of one tile alone.  With the
 // reactions and species spread over lanes a node took about 150 wavefront instructions, 27 % of them FP64
 // arithmetic; here it takes 58, 62 % of them FP64.  Measured per stage (9 species, N_p = 3): E = 2^18 374 us
 // in the best spread form, 149 here; E = 2^16 99 and 48; 1024 instances of 128..4096 elements, N_p = 2 and
-// 3, 1713 and 565; but one instance of 200 elements 12.4 and 17.2.  The tile of three wavefronts beat a
+// 3, 1713 and 565; but one instance of 200 elements 11.6 and 16.9.  The tile of three wavefronts beat a
 // tile of one (no barriers, but a third of its lanes idle in the chemistry: 178 at E = 2^18).
 #include "adg_ns_device.hpp"
 
