@@ -198,7 +198,6 @@ adg_status enqueue_step(adg_solver *s, hipStream_t st, TimerFn timer) {
 // have been stepped by replays since the last call: the state goes to the buffer that the host steps from
 // and back, and the first launch relies on no carried AT values.
 hipError_t align(adg_solver *s, bool begin) {
-  if (begin && capturing(s->stream)) s->captured = true;
   if (!s->captured) return hipSuccess;
   s->at_ready = false;
   int cur = 0, par = 0;
@@ -341,8 +340,8 @@ adg_status adg_set_state(adg_solver *s, const double *w, int64_t count, int32_t 
   return ADG_OK;
 }
 
-static adg_status run_steps(adg_solver *s, int n_steps) {
-  if (s->graph_steps > 0) {
+static adg_status run_steps(adg_solver *s, int n_steps, bool graphs) {
+  if (graphs) {
     if (s->graph_built_for != s->graph_steps) {
       adg_status rc = build_graph(s);
       if (rc != ADG_OK) return rc;
@@ -377,8 +376,11 @@ static adg_status run_steps(adg_solver *s, int n_steps) {
 
 adg_status adg_step(adg_solver *s, int32_t n_steps) {
   if (!s || n_steps < 0) return ADG_ERR_ARG;
+  // into a graph of the caller's: plain launches (a graph launched while its stream is captured runs at once)
+  const bool cap = capturing(s->stream);
+  if (cap) s->captured = true;
   HIP_TRY(s, align(s, true));
-  adg_status rc = run_steps(s, n_steps);
+  adg_status rc = run_steps(s, n_steps, s->graph_steps > 0 && !cap);
   if (rc == ADG_OK) HIP_TRY(s, align(s, false));
   return rc;
 }
@@ -401,7 +403,7 @@ adg_status adg_get_state(adg_solver *s, double *w, int64_t count, int32_t where)
   const Layout &L = s->P.lay;
   if (count != (int64_t)L.E * L.V * L.M) return fail(s, ADG_ERR_ARG, "state size mismatch");
   if (!s->host_err && s->noalloc_dev < 0) s->host_err = g_flags.take();
-  if (s->captured) HIP_TRY(s, align(s, true));   // (this call waits, so it is never captured itself)
+  HIP_TRY(s, align(s, true));
   if (where == ADG_HOST) {
     HIP_TRY(s, get_state_host(s->P, s->P.W[s->cur], w, s->host_err, s->stream));
   } else if (where == ADG_DEVICE) {

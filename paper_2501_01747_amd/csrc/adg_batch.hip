@@ -540,9 +540,9 @@ adg_status adg_batch_remove(adg_batch *b, int32_t slot) {
   return ADG_OK;
 }
 
-static adg_status run_batch_steps(adg_batch *b, int n_steps) {
+static adg_status run_batch_steps(adg_batch *b, int n_steps, bool graphs) {
   int done = 0;
-  if (b->graph_steps > 0) {
+  if (graphs) {
     if (!b->graph_valid) {
       adg_status rc = build_batch_graph(b);
       if (rc != ADG_OK) return rc;
@@ -562,9 +562,11 @@ adg_status adg_batch_step(adg_batch *b, int32_t n_steps) {
   adg_status rc = prepare(b);
   if (rc != ADG_OK) return rc;
   if (b->groups.empty()) return ADG_OK;
-  if (capturing(b->stream)) b->captured = true;
+  // into a graph of the caller's: plain launches (a graph launched while its stream is captured runs at once)
+  const bool cap = capturing(b->stream);
+  if (cap) b->captured = true;
   if (b->captured) BHIP(b, launch_level_counts(b->d_step, b->max_inst, b->stream));
-  rc = run_batch_steps(b, n_steps);
+  rc = run_batch_steps(b, n_steps, b->graph_steps > 0 && !cap);
   if (rc == ADG_OK && b->captured) BHIP(b, launch_level_counts(b->d_step, b->max_inst, b->stream));
   return rc;
 }

@@ -119,3 +119,32 @@ def test_batch_steps_in_a_graph(adg, n):
                 np.testing.assert_array_equal(b.state(x), ref.state(y))
         b.close()
         ref.close()
+
+
+def test_steps_in_a_graph_of_a_solver_and_a_batch_that_have_their_own(adg):
+    """Four steps captured where the library would replay its own graphs of two."""
+    import torch
+
+    c0, w0 = gen.case_c0(E=130, n_pe=8, pmf=(0.3, 0.4, 0.3))
+    c1, w1 = gen.case_c1(E=40, order_p=2, n_pe=4, cfl=0.08, Lx=0.01 * 40 / 2048)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s, ref = adg.Solver(c0), adg.Solver(c0)
+        b, bref = (adg.Batch(1, 40, adg.Batch.instance_bytes(c1)) for _ in range(2))
+        for x in (s, ref):
+            x.set_state(w0)
+        for x in (b, bref):
+            x.add(c1, w1)
+        for x, r in ((s, ref), (b, bref)):
+            x.set_graph(2)
+            x.step(4)
+            g = capture(x, 4)
+            g.replay()
+            x.step(3)
+            g.replay()
+            r.step(15)
+        np.testing.assert_array_equal(s.state(), ref.state())
+        np.testing.assert_array_equal(b.state(0), bref.state(0))
+        assert s.step_count() == 15 and b.poll()[0][0] == 15
+        for x in (s, ref, b, bref):
+            x.close()
