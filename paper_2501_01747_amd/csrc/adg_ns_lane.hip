@@ -181,8 +181,9 @@ __device__ __forceinline__ void ns_lane_tile(const NsArgs &a, const double *__re
 
   // The mechanism's records into the scalar cache: a wavefront of a small launch would miss on each in turn
   // (16 species, E = 2^16, N_p = 3: 100 -> 86 us a stage).  The loads go out before those of the modes, in
-  // whose shadow they return; issued after them, the wait took 3800 of a tile's 41000 cycles (batches of
-  // up to 150 tiles 55 -> 51.5 us a step, E = 2^18 153 -> 149 a stage, and 1024 instances 602 -> 565).
+  // whose shadow they return; issued after them, the wait took 3800 of a tile's 41000 cycles, and the batched
+  // kernel kept 24 bytes of scratch per lane (up to 150 tiles 55 -> 51.5 us a step, E = 2^18 153 -> 149 a
+  // stage, 1024 instances 602 -> 565; a stage of 4096 instances 5.9 -> 4.9 GB of HBM traffic).
   int pre[kPre];
   {
     const auto *line = (const __attribute__((address_space(4))) int *)(uintptr_t)&static_cast<const NsMechT<NS> *>(a.mech)->sp[0];
